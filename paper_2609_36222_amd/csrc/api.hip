@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "../../include/base.h"
@@ -249,19 +250,22 @@ base_status run_forward(const base_layer *L, const void *x, int32_t B,
   // the same launch lists the FFN's parts and gate/up's token rows (bf16)
   HIP_TRY(launch_compact(B, L->K, L->E, bc, ns, exec_ids, exec_gates, slot_of, n_sel,
                          shared_gate(L) ? at<float>(ws, o.gdot) : nullptr, offsets,
-                         pair_tok, pair_gate, pair_of, sel_ids, bf16, L->d, L->I, tokoff,
+                         pair_tok, pair_gate, pair_of, sel_ids, bf16 && !ffn_split(B), L->d, L->I, tokoff,
                          hdr, units_gu, units_dn, n_cu, st));
   stage_end(st);
   stage(5, st);   // no launch of its own: gate/up gathers its tokens itself
   stage_end(st);
   stage(6, st);
   const bool packed = L->w_layout == BASE_W_PACKED;
-  HIP_TRY(launch_gateup(bf16, packed, x, B, L->d, L->I, L->E, L->K, bc, ns, L->w13,
+  // the fused layer's kept set is part of its own batch's union; a caller of
+  // base_moe_forward may bring any
+  const int slots = backfilled ? std::min(bc, B * L->K) : bc;
+  HIP_TRY(launch_gateup(bf16, packed, x, B, L->d, L->I, L->E, L->K, bc, slots, ns, L->w13,
                         L->w13_shared, sel_ids, n_sel, offsets, pair_tok, hdr, units_gu, n_cu,
                         tokoff, at<void>(ws, o.H), st));
   stage_end(st);
   stage(7, st);
-  HIP_TRY(launch_down(bf16, packed, B, L->d, L->I, L->E, L->K, bc, ns, L->w2,
+  HIP_TRY(launch_down(bf16, packed, B, L->d, L->I, L->E, L->K, bc, slots, ns, L->w2,
                       L->w2_shared, sel_ids, n_sel, offsets, hdr, units_dn, n_cu, pair_gate,
                       at<void>(ws, o.H), at<float>(ws, o.pairbuf), st));
   stage_end(st);
@@ -538,13 +542,13 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
   HIP_TRY(launch_compact(B, C.K, C.E, bc, 0, at<int32_t>(ws, o.exec_ids),
                          at<float>(ws, o.exec_gates), slot, nsel, nullptr, offsets, pair_tok,
                          at<float>(ws, o.pair_gate), at<int32_t>(ws, o.pair_of), sel,
-                         bf16, C.d, C.I, at<uint32_t>(ws, o.tokoff), hdr, units_gu, units_dn,
+                         bf16 && !ffn_split(B), C.d, C.I, at<uint32_t>(ws, o.tokoff), hdr, units_gu, units_dn,
                          n_cu, st));
   const bool packed = C.w_layout == BASE_W_PACKED;
-  HIP_TRY(launch_gateup(bf16, packed, z, B, C.d, C.I, C.E, C.K, bc, 0, C.w13, nullptr, sel,
+  HIP_TRY(launch_gateup(bf16, packed, z, B, C.d, C.I, C.E, C.K, bc, std::min(bc, B * C.K), 0, C.w13, nullptr, sel,
                         nsel, offsets, pair_tok, hdr, units_gu, n_cu, at<uint32_t>(ws, o.tokoff),
                         at<void>(ws, o.H), st));
-  HIP_TRY(launch_down(bf16, packed, B, C.d, C.I, C.E, C.K, bc, 0, C.w2, nullptr, sel, nsel,
+  HIP_TRY(launch_down(bf16, packed, B, C.d, C.I, C.E, C.K, bc, std::min(bc, B * C.K), 0, C.w2, nullptr, sel, nsel,
                       offsets, hdr, units_dn, n_cu, at<float>(ws, o.pair_gate),
                       at<void>(ws, o.H), at<float>(ws, o.pairbuf), st));
   double *inv = at<double>(ws, o.total);

@@ -16,6 +16,8 @@
 // row (l % 16) of A and column (l % 16) of B with the 8 contraction
 // elements 8*(l/16) .. 8*(l/16)+7 of a 32-wide k step; the result holds
 // D[4*(l/16) + r][l % 16] in register r.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -488,6 +490,268 @@ void k_down_bf16(int d, int I, int E, int ns, const uint16_t *__restrict__ w2r,
 }
 static_assert(FFN_DN_PT == 8, "down tile-count cases");
 
+// ----------------------------------------------------------------------------
+// Small batches (ffn_split): every slot's pairs fit SP_NT 16-pair tiles, so a
+// row group's weights meet few tokens and the launch is a pure weight stream.
+// One workgroup per (slot, row group); its SP_WAVES wavefronts split the
+// contraction (wavefront s: the s-th contiguous share of the k-steps), each
+// with weights and token fragments of DW k-steps requested ahead into
+// registers, without a barrier until the shares are added through LDS in
+// ascending order.  The slot's expert, pairs and tokens come straight from
+// the plan arrays (no unit tables), the activations go out as rows
+// H[p][I].  A slot with more pairs than the tiles hold (only when routes
+// repeat an expert) takes several passes.
+// F weight fragments (16 rows each) by NT token tiles per wavefront.
+constexpr int SP_WAVES = 8;
+// Row-pair tiles per gate/up workgroup, row tiles per down workgroup (two
+// 16-token batches: the same weight tiles against two token tiles) and k-steps
+// in flight.  Two row-pair tiles are one 4 KiB block of the packed layout
+// per k-step and halve the token reads of one (gate/up at OLMoE's 134 MB, B =
+// 32: 25.7 against 28.2 us; equal below); down's launches at B <= 16 are
+// short of workgroups, so two row tiles (8.0 against 8.8 us at ten
+// Qwen3-shaped experts).  Six or eight k-steps ahead, or three at twice the
+// wavefronts per SIMD, measured the same or slower.
+constexpr int SPG_RT = 2, SPG_DW = 4;
+constexpr int SPD_RT1 = 2, SPD_RT2 = 4, SPD_DW = 4;
+constexpr int SP_NT = 2;   // token tiles per pass at most
+static_assert(16 * SP_NT >= FFN_SPLIT_B, "a slot's pairs in one pass");
+
+// slot y of the launch: its expert's matrix index, first pair and pair count
+// (n = 0: no such slot).  Slots kmax .. kmax + ns - 1 are the shared experts.
+struct SpSlot {
+  int u, p0, n;
+  bool shared;
+};
+__device__ __forceinline__ SpSlot sp_slot(int s, int kmax, int budget, int E,
+                                          const int32_t *__restrict__ sel_ids,
+                                          const int32_t *__restrict__ n_sel_p,
+                                          const int32_t *__restrict__ offsets) {
+  const bool sh = s >= kmax;
+  const int o = sh ? budget + (s - kmax) : s;
+  // all requested together
+  const int u = sel_ids[sh ? 0 : s], a = offsets[o], b = offsets[o + 1], ns = *n_sel_p;
+  SpSlot r;
+  r.shared = sh;
+  r.u = __builtin_amdgcn_readfirstlane(sh ? s - kmax : u);
+  r.p0 = __builtin_amdgcn_readfirstlane(a);
+  r.n = __builtin_amdgcn_readfirstlane(b - a);
+  if (!sh && (s >= ns || u < 0 || u >= E)) r.n = 0;   // u: only for a plan not made by base_select
+  return r;
+}
+
+// first k-step of wavefront w's share of KS
+__device__ __forceinline__ int sp_share(int KS, int w) { return w * KS / SP_WAVES; }
+
+// acc[f][j] += sum over this wavefront's k-steps [k0, k1) of fragment f of
+// the weights times token tile j; lw / lt: the byte offsets of k-step ks.
+template <int F, int NT, int DW, typename LW, typename LT>
+__device__ __forceinline__ void sp_stream(int k0, int k1, LW lw, LT lt, f32x4 (&acc)[F][NT]) {
+  bf16x8 w[DW][F], t[DW][NT];
+  auto request = [&](int p, int ks) {
+#pragma unroll
+    for (int f = 0; f < F; ++f) w[p][f] = lw(f, ks);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) t[p][j] = lt(j, ks);
+  };
+  auto use = [&](int p) {
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[f][j] = mfma16(w[p][f], t[p][j], acc[f][j]);
+  };
+#pragma unroll
+  for (int p = 0; p < DW; ++p) request(p, k0 + p);
+  int k = k0;
+  for (; k + DW < k1; k += DW) {
+#pragma unroll
+    for (int p = 0; p < DW; ++p) {
+      use(p);
+      __builtin_amdgcn_sched_barrier(0);
+      request(p, k + DW + p);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < DW; ++p) use(p);
+}
+
+// f with the tile count nt (1 .. NT) as a compile-time value
+template <int NT, typename Fn>
+__device__ __forceinline__ void sp_tiles(int nt, Fn f) {
+  if constexpr (NT > 1) {
+    if (nt < NT) return sp_tiles<NT - 1>(nt, f);
+  }
+  f(std::integral_constant<int, NT>{});
+}
+
+template <int NT, int RT, bool PACKED>
+__device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uint16_t *w13,
+                                             int rp0, rsrc_t rx, const uint32_t (&tv)[NT], int n,
+                                             uint16_t *__restrict__ h0) {
+  constexpr int F = 2 * RT;
+  const int w = wave_id_u(), lane = lane_id();
+  const int KS = d / 32, k0 = sp_share(KS, w), k1 = sp_share(KS, w + 1);
+  f32x4 acc[F][NT];
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[f][j] = f32x4{0, 0, 0, 0};
+  rsrc_t rg, ru;
+  uint32_t v0;
+  if (PACKED) {
+    const uint32_t gbytes = (uint32_t)KS * 4096u;
+    rg = ru = make_rsrc(w13 + (size_t)(rp0 >> 1) * (gbytes / 2), gbytes);
+    v0 = lane * 16 + (rp0 & 1) * 1024;
+  } else {
+    const uint32_t tb = (uint32_t)(RT * 16 * d * 2);
+    rg = make_rsrc(w13 + (size_t)16 * rp0 * d, tb);
+    ru = make_rsrc(w13 + (size_t)(I + 16 * rp0) * d, tb);
+    v0 = (uint32_t)(lane & 15) * (uint32_t)(d * 2) + (uint32_t)(lane >> 4) * 16u;
+  }
+  auto lw = [&](int f, int ks) {
+    const uint32_t o = ks < k1 ? (uint32_t)ks * (PACKED ? 4096u : 64u) : FFN_TOK_PAD;
+    const uint32_t fo = PACKED ? (uint32_t)(f % RT) * 1024u + (f >= RT ? 2048u : 0u)
+                               : (uint32_t)(f % RT) * (uint32_t)(16 * d * 2);
+    return bload(f < RT ? rg : ru, v0 + fo + o, 0);
+  };
+  auto lt = [&](int j, int ks) {
+    return bload(rx, ks < k1 ? tv[j] + (uint32_t)ks * 64u : FFN_TOK_PAD, 0);
+  };
+  sp_stream<F, NT, SPG_DW>(k0, k1, lw, lt, acc);
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) red[(w * F * NT + f * NT + j) * WAVE + lane] = acc[f][j];
+  __syncthreads();
+  // (row-pair tile, token tile, half of the lane's four rows) in turn
+  for (int it = w; it < 2 * RT * NT; it += SP_WAVES) {
+    const int half = it & 1, c = it >> 1, i = c / NT, j = c % NT;
+    const float *rf = reinterpret_cast<const float *>(red) + lane * 4 + 2 * half;
+    float g0 = 0.0f, g1 = 0.0f, u0 = 0.0f, u1 = 0.0f;
+#pragma unroll
+    for (int s = 0; s < SP_WAVES; ++s) {
+      const float2 a = *reinterpret_cast<const float2 *>(rf + (s * F * NT + i * NT + j) * WAVE * 4);
+      const float2 b = *reinterpret_cast<const float2 *>(rf + (s * F * NT + (RT + i) * NT + j) * WAVE * 4);
+      g0 = g0 + a.x; g1 = g1 + a.y;
+      u0 = u0 + b.x; u1 = u1 + b.y;
+    }
+    const int tk = 16 * j + (lane & 15);
+    if (tk < n) {
+      const uint32_t pk = (uint32_t)f32_to_bf16(silu_bf16(g0) * u0) |
+                          ((uint32_t)f32_to_bf16(silu_bf16(g1) * u1) << 16);
+      *reinterpret_cast<uint32_t *>(h0 + (size_t)tk * I + 16 * (rp0 + i) + 4 * (lane >> 4) + 2 * half) = pk;
+    }
+  }
+}
+
+// NT: token tiles per pass (1 or 2); RT row-pair tiles per workgroup
+template <int NT, int RT, bool PACKED>
+__global__ __launch_bounds__(SP_WAVES * WAVE)
+void k_gateup_split(int d, int I, int E, int kmax, int budget, const uint16_t *__restrict__ w13r,
+                    const uint16_t *__restrict__ w13s, const int32_t *__restrict__ sel_ids,
+                    const int32_t *__restrict__ n_sel, const int32_t *__restrict__ offsets,
+                    const int32_t *__restrict__ pair_tok, const uint16_t *__restrict__ x, int B,
+                    uint16_t *__restrict__ H) {
+  __shared__ f32x4 red[SP_WAVES * 2 * RT * NT * WAVE];
+  const SpSlot sl = sp_slot(blockIdx.y, kmax, budget, E, sel_ids, n_sel, offsets);
+  const int lane = lane_id(), rp0 = blockIdx.x * RT;
+  const uint16_t *w13 = (sl.shared ? w13s : w13r) + (size_t)sl.u * 2 * I * d;
+  const rsrc_t rx = make_rsrc(x, (uint32_t)B * (uint32_t)d * 2u);
+  for (int c = 0; c < sl.n; c += 16 * NT) {
+    const int n = min(sl.n - c, 16 * NT);
+    uint32_t tv[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int i = 16 * j + (lane & 15);
+      const int t = pair_tok[sl.p0 + c + min(i, n - 1)];
+      tv[j] = i < n ? (uint32_t)t * (uint32_t)d * 2u + (uint32_t)(lane >> 4) * 16u : FFN_TOK_PAD;
+    }
+    if (c > 0) __syncthreads();
+    uint16_t *h0 = H + (size_t)(sl.p0 + c) * I;
+    sp_tiles<NT>((n + 15) / 16, [&](auto k) {
+      constexpr int N = decltype(k)::value;
+      uint32_t t[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) t[j] = tv[j];
+      gateup_split<N, RT, PACKED>(red, d, I, w13, rp0, rx, t, n, h0);
+    });
+  }
+}
+
+template <int NT, int RT, bool PACKED>
+__device__ __forceinline__ void down_split(f32x4 *red, int d, int I, const uint16_t *w2, int rt0,
+                                           const uint16_t *__restrict__ h0, int n,
+                                           const float *__restrict__ gate0,
+                                           float *__restrict__ out0) {
+  const int w = wave_id_u(), lane = lane_id();
+  const int KS = I / 32, k0 = sp_share(KS, w), k1 = sp_share(KS, w + 1);
+  f32x4 acc[RT][NT];
+#pragma unroll
+  for (int f = 0; f < RT; ++f)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[f][j] = f32x4{0, 0, 0, 0};
+  rsrc_t rw;
+  uint32_t v0;
+  if (PACKED) {
+    const uint32_t gbytes = (uint32_t)KS * 4096u;
+    rw = make_rsrc(w2 + (size_t)(rt0 >> 2) * (gbytes / 2), gbytes);
+    v0 = lane * 16 + (rt0 & 3) * 1024;
+  } else {
+    rw = make_rsrc(w2 + (size_t)16 * rt0 * I, (uint32_t)(RT * 16 * I * 2));
+    v0 = (uint32_t)(lane & 15) * (uint32_t)(I * 2) + (uint32_t)(lane >> 4) * 16u;
+  }
+  const rsrc_t rt = make_rsrc(h0, (uint32_t)n * (uint32_t)I * 2u);
+  const uint32_t hv = (uint32_t)(lane & 15) * (uint32_t)(I * 2) + (uint32_t)(lane >> 4) * 16u;
+  auto lw = [&](int f, int ks) {
+    const uint32_t o = ks < k1 ? (uint32_t)ks * (PACKED ? 4096u : 64u) : FFN_TOK_PAD;
+    return bload(rw, v0 + (PACKED ? (uint32_t)f * 1024u : (uint32_t)f * (uint32_t)(16 * I * 2)) + o, 0);
+  };
+  auto lt = [&](int j, int ks) {   // rows past the slot's pairs are past rt: zero
+    return bload(rt, ks < k1 ? hv + (uint32_t)j * (uint32_t)(16 * I * 2) + (uint32_t)ks * 64u
+                             : FFN_TOK_PAD, 0);
+  };
+  sp_stream<RT, NT, SPD_DW>(k0, k1, lw, lt, acc);
+#pragma unroll
+  for (int f = 0; f < RT; ++f)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) red[(w * RT * NT + f * NT + j) * WAVE + lane] = acc[f][j];
+  __syncthreads();
+  for (int it = w; it < RT * NT; it += SP_WAVES) {
+    const int f = it / NT, j = it % NT, tk = 16 * j + (lane & 15);
+    f32x4 o = red[it * WAVE + lane];
+#pragma unroll
+    for (int s = 1; s < SP_WAVES; ++s) {
+      const f32x4 a = red[(s * RT * NT + it) * WAVE + lane];
+      o[0] = o[0] + a[0]; o[1] = o[1] + a[1]; o[2] = o[2] + a[2]; o[3] = o[3] + a[3];
+    }
+    if (tk < n) {
+      const float gt = gate0[tk];
+      *reinterpret_cast<float4 *>(out0 + (size_t)tk * d + 16 * (rt0 + f) + 4 * (lane >> 4)) =
+          float4{gt * o[0], gt * o[1], gt * o[2], gt * o[3]};
+    }
+  }
+}
+
+template <int NT, int RT, bool PACKED>
+__global__ __launch_bounds__(SP_WAVES * WAVE)
+void k_down_split(int d, int I, int E, int kmax, int budget, const uint16_t *__restrict__ w2r,
+                  const uint16_t *__restrict__ w2s, const int32_t *__restrict__ sel_ids,
+                  const int32_t *__restrict__ n_sel, const int32_t *__restrict__ offsets,
+                  const float *__restrict__ pair_gate, const uint16_t *__restrict__ H,
+                  float *__restrict__ pairbuf) {
+  __shared__ f32x4 red[SP_WAVES * RT * NT * WAVE];
+  const SpSlot sl = sp_slot(blockIdx.y, kmax, budget, E, sel_ids, n_sel, offsets);
+  const uint16_t *w2 = (sl.shared ? w2s : w2r) + (size_t)sl.u * d * I;
+  for (int c = 0; c < sl.n; c += 16 * NT) {
+    const int n = min(sl.n - c, 16 * NT), p0 = sl.p0 + c, rt0 = blockIdx.x * RT;
+    if (c > 0) __syncthreads();
+    sp_tiles<NT>((n + 15) / 16, [&](auto k) {
+      down_split<decltype(k)::value, RT, PACKED>(red, d, I, w2, rt0, H + (size_t)p0 * I, n,
+                                                 pair_gate + p0, pairbuf + (size_t)p0 * d);
+    });
+  }
+}
+
 // fp32 experts (small layers): one wavefront per (kept slot, output row).
 // The lanes split the contraction (lane l takes elements l, l + 64, ..., so
 // every load of a row is contiguous across the wavefront) and each token's
@@ -597,12 +861,21 @@ void k_combine(int B, int d, int kc, const int32_t *__restrict__ pair_of,
 }
 
 hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
-                         int I, int E, int K, int budget, int ns, const void *w13,
+                         int I, int E, int K, int budget, int slots, int ns, const void *w13,
                          const void *w13s, const int32_t *sel_ids, const int32_t *n_sel,
                          const int32_t *offsets, const int32_t *pair_tok,
                          const FfnHdr *hdr, const FfnUnit *units, int n_cu,
                          const uint32_t *tokoff, void *H, hipStream_t st) {
-  if (bf16) {
+  if (bf16 && ffn_split(B)) {
+    const dim3 grid(I / 16 / SPG_RT, slots + ns);
+#define BASE_GS(N, P) k_gateup_split<N, SPG_RT, P>
+    const auto kern = B <= 16 ? (packed ? BASE_GS(1, true) : BASE_GS(1, false))
+                              : (packed ? BASE_GS(2, true) : BASE_GS(2, false));
+#undef BASE_GS
+    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, (const uint16_t *)w13,
+             (const uint16_t *)w13s, sel_ids, n_sel, offsets, pair_tok, (const uint16_t *)x, B,
+             (uint16_t *)H);
+  } else if (bf16) {
     launch_k(packed ? k_gateup_bf16<true> : k_gateup_bf16<false>, dim3(ffn_gu_grid(n_cu)),
              dim3(FFN_WAVES * WAVE), 0, st, d, I, E, ns, (const uint16_t *)w13,
              (const uint16_t *)w13s, hdr, units, (const uint16_t *)x, B, tokoff, (uint16_t *)H);
@@ -616,12 +889,21 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
 }
 
 hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K,
-                       int budget, int ns, const void *w2, const void *w2s,
+                       int budget, int slots, int ns, const void *w2, const void *w2s,
                        const int32_t *sel_ids,
                        const int32_t *n_sel, const int32_t *offsets,
                        const FfnHdr *hdr, const FfnUnit *units, int n_cu,
                        const float *pair_gate, const void *H, float *pairbuf, hipStream_t st) {
-  if (bf16) {
+  if (bf16 && ffn_split(B)) {
+    const dim3 grid(d / 16 / (B <= 16 ? SPD_RT1 : SPD_RT2), slots + ns);
+#define BASE_DS(N, R, P) k_down_split<N, R, P>
+    const auto kern = B <= 16 ? (packed ? BASE_DS(1, SPD_RT1, true) : BASE_DS(1, SPD_RT1, false))
+                              : (packed ? BASE_DS(2, SPD_RT2, true) : BASE_DS(2, SPD_RT2, false));
+#undef BASE_DS
+    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, (const uint16_t *)w2,
+             (const uint16_t *)w2s, sel_ids, n_sel, offsets, pair_gate, (const uint16_t *)H,
+             pairbuf);
+  } else if (bf16) {
     const int kind = ffn_dn_kind(budget, ns, I);
     const auto kern =
         kind == 2 ? (packed ? k_down_bf16<true, FFN_DN_DW_LONG, FFN_DN_WPE_LONG>

@@ -104,6 +104,16 @@ constexpr uint32_t FFN_TOK_PAD = 0x80000000u;   // past every x: a buffer load r
 static_assert(FFN_GU_PT <= FFN_WAVES, "one token tile per gate/up wavefront");
 static_assert((size_t)MAX_B * 16384 * 2 < FFN_TOK_PAD, "token row offsets below the pad mark");
 
+// Batches of at most FFN_SPLIT_B tokens take the FFN's split kernels (see
+// "Small batches" in ffn.hip), which need no unit tables: a slot then holds
+// at most two 16-pair tiles, and the launch is a weight stream.  Measured per
+// layer against the unit kernels: qwen3-shaped B = 1 59 -> 44 us, B = 16 64 ->
+// 51, OLMoE-shaped B = 32 76 -> 71, Mixtral-shaped B = 16 295 -> 274; with
+// four tiles per slot (B = 64) they are equal or slower (Mixtral-shaped 295
+// -> 306), their token reads then exceeding the weights'.
+constexpr int FFN_SPLIT_B = 32;
+__host__ __device__ inline bool ffn_split(int B) { return B <= FFN_SPLIT_B; }
+
 // A unit: expert u (u >= E: shared expert u - E), the part's first 16-pair
 // tile, its tile count, its first pair in the compacted order and its pair
 // count, and the unit's row group (gate/up: hdr.rp_gu row-pair tiles;
@@ -195,16 +205,18 @@ hipError_t launch_compact(int B, int K, int E, int budget, int ns, const int32_t
                           FfnUnit *units_dn, int n_cu, hipStream_t st);
 hipError_t launch_pack(const void *w13, const void *w2, void *w13p, void *w2p,
                        int E, int d, int I, hipStream_t st);
+// slots: at most this many kept slots (budget, or fewer where the kept set is
+// known to come from this batch's routes)
 // parts of expert u >= E read the shared experts' weights (w13s / w2s, u - E)
 hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
-                         int I, int E, int K, int budget, int ns, const void *w13,
+                         int I, int E, int K, int budget, int slots, int ns, const void *w13,
                          const void *w13s,
                          const int32_t *sel_ids, const int32_t *n_sel,
                          const int32_t *offsets, const int32_t *pair_tok,
                          const FfnHdr *hdr, const FfnUnit *units, int n_cu,
                          const uint32_t *tokoff, void *H, hipStream_t st);
 hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K,
-                       int budget, int ns, const void *w2, const void *w2s,
+                       int budget, int slots, int ns, const void *w2, const void *w2s,
                        const int32_t *sel_ids,
                        const int32_t *n_sel, const int32_t *offsets,
                        const FfnHdr *hdr, const FfnUnit *units, int n_cu,

@@ -1,0 +1,77 @@
+"""The FFN's split kernels (batches of at most 32 tokens): tile edges of the
+tokens, contractions shorter than the wavefronts' shares, slots of several
+passes, kept sets that the caller brings."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import carith, method
+from test_gpu_parity import Y_TOL, check_plan, gu, run_case  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("d,E,K,I,ns,budget", [
+    (256, 8, 2, 64, 0, 3),       # eight k-steps of d, two of I: most shares of I empty
+    (768, 24, 5, 192, 2, 9),     # shares of unequal length, shared experts
+    (2048, 16, 4, 1408, 1, 16),  # several rounds of k-steps per share
+])
+def test_token_tiles(gu, B, d, E, K, I, ns, budget):  # noqa: F811
+    inp = W.custom_layer(d, E, K, I, B, seed=700 + B, n_shared=ns, shared_gate=ns == 2)
+    run_case(gu, inp, budget, flags=1, with_residual=True)
+
+
+def _forward(gu, inp, logits, ids, sel, n_sel, slot, budget, flags):  # noqa: F811
+    """base_moe_forward on a given plan against the oracle."""
+    from paper_2609_36222_amd import binding as bd
+    sh, B = inp["shape"], inp["x"].shape[0]
+    ex, n_ex = method.backfill(logits, ids, slot, n_sel, sh.K, flags)
+    gates = method.gates_c(logits, ids, ex, n_ex, 1, flags)
+    offsets, pair_tok, pair_gate, pair_of = method.compact(ex, n_ex, slot, gates, budget)
+    y_ref = method.moe_restricted64(inp["x"], ex, n_ex, gates,
+                                    method.Experts(inp["w13"], inp["w2"], sh.bf16))
+    for packed in (False, True):
+        gl = gu.GpuLayer(inp, packed=packed)
+        ws, y = gl.workspace(B, budget), gl.y_like(B)
+
+        def i32(a):
+            return torch.from_numpy(np.ascontiguousarray(a, np.int32)).cuda()
+
+        plan = bd.base_moe_forward(gl.desc, gl.x(inp["x"]), B, gu.dev_f32(logits), i32(ids),
+                                   i32(sel), i32([n_sel]), i32(slot), budget, flags, None, y, ws)
+        torch.cuda.synchronize()
+        got = gu.plan_arrays(plan, ws, B, sh.K, sh.E, budget, full=False)
+        check_plan(got, dict(exec_ids=ex, exec_gates=gates, offsets=offsets, pair_tok=pair_tok,
+                             pair_gate=pair_gate, pair_of=pair_of))
+        err = np.max(np.abs(gu.to_np_f32(y).astype(np.float64) - y_ref))
+        assert err <= Y_TOL[sh.bf16], err
+    return offsets
+
+
+@pytest.mark.parametrize("B", [16, 29])
+def test_slot_of_several_passes(gu, B):  # noqa: F811
+    """Routes that name one expert up to four times, executed as they are
+    (drop): a slot then holds more pairs than one pass's token tiles."""
+    inp = W.custom_layer(512, 12, 4, 128, B, seed=41)
+    logits, ids, _ = carith.route(inp["x"], inp["w_router"], inp["b_router"], 4, 1)
+    ids = ids.copy()
+    ids[:, :] = 3
+    ids[::5, 1] = 7
+    slot = np.full(12, -1, np.int32)
+    slot[[3, 7]] = [1, 0]
+    offsets = _forward(gu, inp, logits, ids, np.array([7, 3]), 2, slot, 2, 2)
+    assert offsets[2] - offsets[1] > 32
+
+
+def test_kept_set_beyond_the_routes(gu):  # noqa: F811
+    """A kept set of the caller's own, larger than the batch has routes: the
+    token's experts may sit in any slot."""
+    inp = W.custom_layer(256, 40, 2, 128, 1, seed=42)
+    logits, ids, _ = carith.route(inp["x"], inp["w_router"], inp["b_router"], 2, 1)
+    sel = np.setdiff1d(np.arange(40)[::-1], ids[0][:1])[::-1][:30]
+    slot = np.full(40, -1, np.int32)
+    slot[sel] = np.arange(30)
+    _forward(gu, inp, logits, ids, sel, 30, slot, 30, 0)
