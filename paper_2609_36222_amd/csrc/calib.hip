@@ -7,13 +7,16 @@
 // The expert outputs come from the layer's own FFN run with every routed
 // expert kept and unit gates, so one batch costs one dense routed MoE pass.
 //
-// k_calib_norm     inv[t] = 1 / ||x_t|| (0 for x = 0), fp64, and the rows
-//                  z_bar_t = fp32(x_t inv[t]) the Gram reads (plus a zero row)
-// k_calib_pairs    y[p] = log(sum_c out_p[c]^2 + eps), fp64, one workgroup per pair
-// k_calib_moments  per (kept slot, 256 columns): the fp64 sums, pairs in order
-// k_calib_gram     per (kept slot, 128 x 128 block of the upper triangle):
-//                  G += sum_p z_i z_j on the matrix cores (fp32 products and
-//                  sums over the slot's pairs, then one add), mirrored
+// k_calib_norm     inv[t] = 1 / ||x_t|| (0 for x = 0), fp64, and the rows the
+//                  Gram reads (plus a zero row): fp32 layers z_bar_t =
+//                  fp32(x_t inv[t]), bf16 layers x_t times a power of two
+// k_calib_pairs    y[p] = log(sum_c out_p[c]^2 + eps), fp64, one wavefront per pair
+// k_calib_moments  per (kept slot, 128 columns): the fp64 sums, the pairs
+//                  dealt to eight wavefronts
+// k_calib_gram, k_calib_gram_bf16
+//                  per (kept slot, 128 x 128 block of the upper triangle):
+//                  G += sum_p z_i z_j on the matrix cores (fp32 sums over the
+//                  slot's pairs, then one add), mirrored
 // Every statistic has a single writer and a fixed summation order: the
 // results are deterministic.
 #include "common.hpp"
@@ -24,93 +27,224 @@ namespace basek {
 constexpr int CAL_THREADS = 256;
 constexpr double CAL_EPS = 1e-12;
 
-__device__ __forceinline__ double act(const void *x, bool bf16, size_t i) {
-  return bf16 ? (double)bf16_to_f32(((const uint16_t *)x)[i]) : (double)((const float *)x)[i];
-}
-
-// Fixed-order fp64 tree over the workgroup's CAL_THREADS values.
-__device__ __forceinline__ double block_sum(double v, double *sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int h = CAL_THREADS / 2; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + h];
-    __syncthreads();
+// Elements c, c + 1 of an activation row.
+__device__ __forceinline__ double2 act2(const void *row, bool bf16, int c) {
+  if (bf16) {
+    const uint32_t v = *reinterpret_cast<const uint32_t *>((const uint16_t *)row + c);
+    return {(double)__uint_as_float(v << 16), (double)__uint_as_float(v & 0xFFFF0000u)};
   }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
+  const float2 v = *reinterpret_cast<const float2 *>((const float *)row + c);
+  return {(double)v.x, (double)v.y};
 }
 
+// Elements c .. c + 7 (exact widening).
+__device__ __forceinline__ void load8(const void *row, bool bf16, int c, float (&v)[8]) {
+  if (bf16) {
+    const u32x4 r = *reinterpret_cast<const u32x4 *>((const uint16_t *)row + c);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(r[i] << 16);
+      v[2 * i + 1] = __uint_as_float(r[i] & 0xFFFF0000u);
+    }
+  } else {
+    float a[4], b[4];
+    load4((const float *)row + c, a);
+    load4((const float *)row + c + 4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = a[i];
+      v[4 + i] = b[i];
+    }
+  }
+}
+
+// Fixed-order fp64 sum over the wavefront (every lane gets it).
+__device__ __forceinline__ double wave_sum64(double v) {
+#pragma unroll
+  for (int h = WAVE / 2; h >= 1; h >>= 1) v = v + __shfl_xor(v, h, WAVE);
+  return v;
+}
+
+// What the Gram reads.  fp32 layers: rows z_bar_t = fp32(x_t inv[t]); bf16
+// layers: bf16 rows xs_t = x_t 2^k (exact) with 1 <= ||xs_t|| < 2, and sc[t] =
+// fp32(1 / ||xs_t||^2), so that z_i z_j = xs_i (xs_j sc) whatever the scale of
+// x.  d elements a row, B + 1 rows; row B (and sc[B]) are zero.
+struct GramRows {
+  float *z;
+  uint16_t *xs;
+  float *sc;
+};
+
+// One wavefront per token (and one for the zero row).
 __global__ __launch_bounds__(CAL_THREADS)
 void k_calib_norm(const void *__restrict__ x, int bf16, int B, int d, double *__restrict__ inv,
-                  float *__restrict__ zbuf) {
-  __shared__ double sh[CAL_THREADS];
-  const int t = blockIdx.x;
-  if (t >= B) return;
-  double s = 0.0;
-  for (int c = threadIdx.x; c < d; c += CAL_THREADS) {
-    const double v = act(x, bf16, (size_t)t * d + c);
-    s = fma(v, v, s);
+                  GramRows gr) {
+  const int t = blockIdx.x * (CAL_THREADS / WAVE) + threadIdx.x / WAVE, lane = lane_id();
+  if (t > B) return;
+  if (t == B) {
+    const int words = bf16 ? d / 2 : d;
+    uint32_t *z = (bf16 ? (uint32_t *)gr.xs : (uint32_t *)gr.z) + (size_t)B * words;
+    for (int c = lane; c < words; c += WAVE) z[c] = 0u;
+    if (bf16 && lane == 0) gr.sc[B] = 0.0f;
+    return;
   }
-  s = block_sum(s, sh);
+  const size_t at = (size_t)t * d;
+  const void *row = bf16 ? (const void *)((const uint16_t *)x + at) : (const void *)((const float *)x + at);
+  // eight elements per lane and piece
+  double s = 0.0;
+#pragma unroll 4
+  for (int c = 8 * lane; c < d; c += 8 * WAVE) {
+    float v[8];
+    load8(row, bf16, c, v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s = fma((double)v[i], (double)v[i], s);
+  }
+  s = wave_sum64(s);
   const double iv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
-  if (threadIdx.x == 0) inv[t] = iv;
-  for (int c = threadIdx.x; c < d; c += CAL_THREADS)
-    zbuf[(size_t)t * d + c] = (float)(act(x, bf16, (size_t)t * d + c) * iv);
-  if (t == 0)   // the zero row B
-    for (int c = threadIdx.x; c < d; c += CAL_THREADS) zbuf[(size_t)B * d + c] = 0.0f;
+  if (lane == 0) inv[t] = iv;
+  if (bf16) {
+    int e = 0;
+    if (s > 0.0) (void)frexp(sqrt(s), &e);   // ||x|| = m 2^e, 1/2 <= m < 1
+    const int k = 1 - e;
+    const double is = ldexp(iv, -k);
+    if (lane == 0) gr.sc[t] = (float)(is * is);   // 1 / ||xs||^2 (0 for x = 0)
+#pragma unroll 4
+    for (int c = 8 * lane; c < d; c += 8 * WAVE) {
+      float v[8];
+      load8(row, true, c, v);
+      u32x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        o[i] = (__float_as_uint(__builtin_ldexpf(v[2 * i], k)) >> 16) |
+               (__float_as_uint(__builtin_ldexpf(v[2 * i + 1], k)) & 0xFFFF0000u);
+      *reinterpret_cast<u32x4 *>(gr.xs + at + c) = o;
+    }
+  } else {
+    for (int c = 8 * lane; c < d; c += 8 * WAVE) {
+      float v[8];
+      load8(row, false, c, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = (float)((double)v[i] * iv);
+      *reinterpret_cast<float4 *>(gr.z + at + c) = float4{v[0], v[1], v[2], v[3]};
+      *reinterpret_cast<float4 *>(gr.z + at + c + 4) = float4{v[4], v[5], v[6], v[7]};
+    }
+  }
 }
 
 // pairs p < offsets[n_slots] (the routed pairs of the kept slots)
 __global__ __launch_bounds__(CAL_THREADS)
 void k_calib_pairs(const float *__restrict__ out, int d, const int32_t *__restrict__ offsets,
                    int n_slots, double *__restrict__ y) {
-  __shared__ double sh[CAL_THREADS];
-  const int p = blockIdx.x;
+  const int p = blockIdx.x * (CAL_THREADS / WAVE) + threadIdx.x / WAVE, lane = lane_id();
   if (p >= offsets[n_slots]) return;
+  const float *row = out + (size_t)p * d;
   double s = 0.0;
-  for (int c = threadIdx.x; c < d; c += CAL_THREADS) {
-    const double v = (double)out[(size_t)p * d + c];
-    s = fma(v, v, s);
+#pragma unroll 8
+  for (int c = 4 * lane; c < d; c += 4 * WAVE) {
+    const float4 v = *reinterpret_cast<const float4 *>(row + c);
+    s = fma((double)v.x, (double)v.x, s);
+    s = fma((double)v.y, (double)v.y, s);
+    s = fma((double)v.z, (double)v.z, s);
+    s = fma((double)v.w, (double)v.w, s);
   }
-  s = block_sum(s, sh);
-  if (threadIdx.x == 0) y[p] = log(s + CAL_EPS);
+  s = wave_sum64(s);
+  if (lane == 0) y[p] = log(s + CAL_EPS);
 }
 
-__global__ __launch_bounds__(CAL_THREADS)
+// One workgroup per (kept slot, 128 columns), two columns per lane.  The
+// slot's pairs come in chunks whose token, 1 / ||x|| and target sit in LDS;
+// wavefront w takes the pairs w, w + 8, ... of a chunk, eight token rows in
+// flight, and the wavefronts' sums are added in order.  (One thread per
+// column walking all pairs, each a chain of dependent loads, took 135 us per
+// batch of 1024 OLMoE-shaped tokens, whose most popular expert sees nearly
+// every token.)
+constexpr int CM_WAVES = 8;
+constexpr int CM_COLS = 2 * WAVE;
+constexpr int CM_CHUNK = CM_WAVES * WAVE;
+__global__ __launch_bounds__(CM_WAVES * WAVE)
 void k_calib_moments(const void *__restrict__ x, int bf16, int d, const double *__restrict__ inv,
                      const int32_t *__restrict__ n_sel, const int32_t *__restrict__ sel_ids,
                      const int32_t *__restrict__ offsets, const int32_t *__restrict__ pair_tok,
                      const double *__restrict__ y, CalibStats st) {
+  __shared__ int tok_s[CM_CHUNK];
+  __shared__ double inv_s[CM_CHUNK], y_s[CM_CHUNK];
+  __shared__ double2 red[2][CM_WAVES][WAVE];
   const int s = blockIdx.x;
   if (s >= *n_sel) return;
   const int u = sel_ids[s];
   const int p0 = offsets[s], p1 = offsets[s + 1];
-  const int j = blockIdx.y * CAL_THREADS + threadIdx.x;
-  if (j < d) {
-    double sz = 0.0, q = 0.0;
-    for (int p = p0; p < p1; ++p) {
-      const int t = pair_tok[p];
-      const double z = act(x, bf16, (size_t)t * d + j) * inv[t];
-      sz = sz + z;
-      q = fma(z, y[p], q);
+  const int tid = threadIdx.x, w = tid / WAVE, lane = lane_id();
+  const int j = blockIdx.y * CM_COLS + 2 * lane;
+  double2 sz = {0.0, 0.0}, q = {0.0, 0.0};
+  double sy = 0.0, syy = 0.0;   // (first column group) lane sums of this wavefront's targets
+  for (int c0 = p0; c0 < p1; c0 += CM_CHUNK) {
+    const int n = min(CM_CHUNK, p1 - c0);
+    if (c0 > p0) __syncthreads();
+    if (tid < n) {
+      const int t = pair_tok[c0 + tid];
+      tok_s[tid] = t;
+      inv_s[tid] = inv[t];
+      const double yv = y[c0 + tid];
+      y_s[tid] = yv;
+      sy = sy + yv;
+      syy = fma(yv, yv, syy);
     }
-    st.sz[(size_t)u * d + j] += sz;
-    st.q[(size_t)u * d + j] += q;
+    __syncthreads();
+    constexpr int AHEAD = 8;
+    for (int i0 = w; i0 < n; i0 += AHEAD * CM_WAVES) {
+      double2 v[AHEAD];
+#pragma unroll
+      for (int a = 0; a < AHEAD; ++a) {
+        const int i = min(i0 + a * CM_WAVES, n - 1);
+        const size_t at = (size_t)tok_s[i] * d;
+        v[a] = act2(bf16 ? (const void *)((const uint16_t *)x + at) : (const void *)((const float *)x + at),
+                    bf16, j);
+      }
+#pragma unroll
+      for (int a = 0; a < AHEAD; ++a) {
+        const int i = i0 + a * CM_WAVES;
+        if (i < n) {
+          const double zx = v[a].x * inv_s[i], zy = v[a].y * inv_s[i];
+          sz.x = sz.x + zx;
+          sz.y = sz.y + zy;
+          q.x = fma(zx, y_s[i], q.x);
+          q.y = fma(zy, y_s[i], q.y);
+        }
+      }
+    }
   }
-  if (blockIdx.y == 0 && threadIdx.x == 0) {
-    double sy = 0.0, syy = 0.0;
-    for (int p = p0; p < p1; ++p) {
-      sy = sy + y[p];
-      syy = fma(y[p], y[p], syy);
+  red[0][w][lane] = sz;
+  red[1][w][lane] = q;
+  __syncthreads();
+  if (w < 2) {   // wavefront 0: sz, 1: q
+    double2 r = red[w][0][lane];
+    for (int i = 1; i < CM_WAVES; ++i) {
+      r.x = r.x + red[w][i][lane].x;
+      r.y = r.y + red[w][i][lane].y;
+    }
+    double *dst = (w == 0 ? st.sz : st.q) + (size_t)u * d + j;
+    dst[0] += r.x;
+    dst[1] += r.y;
+  }
+  if (blockIdx.y != 0) return;
+  __syncthreads();
+  sy = wave_sum64(sy);
+  syy = wave_sum64(syy);
+  if (lane == 0) red[0][w][0] = double2{sy, syy};
+  __syncthreads();
+  if (tid == 0) {
+    double2 r = red[0][0][0];
+    for (int i = 1; i < CM_WAVES; ++i) {
+      r.x = r.x + red[0][i][0].x;
+      r.y = r.y + red[0][i][0].y;
     }
     st.head[(size_t)u * 4 + 0] += (double)(p1 - p0);
-    st.head[(size_t)u * 4 + 1] += sy;
-    st.head[(size_t)u * 4 + 2] += syy;
+    st.head[(size_t)u * 4 + 1] += r.x;
+    st.head[(size_t)u * 4 + 2] += r.y;
   }
 }
 
-// The Gram matrices on the matrix cores (v_mfma_f32_16x16x4_f32: fp32
+// fp32 layers: the Gram matrices on the matrix cores (v_mfma_f32_16x16x4_f32: fp32
 // operands, products and sums).  A workgroup owns one 128 x 128 block (I, J),
 // I <= J, of one kept slot's G_u, and each of its four wavefronts a 64 x 64
 // quarter (rows rb.., columns cb..) as 4 x 4 instruction tiles.  Tile (a, b)
@@ -136,6 +270,9 @@ constexpr int GM_AHEAD = 3;   // steps of operands in flight (ring of 4)
 
 __device__ __forceinline__ f32x4 mfma_f32_4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma_bf16_32(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 __global__ __launch_bounds__(GM_WAVES * WAVE, 2)
@@ -217,6 +354,159 @@ void k_calib_gram(const float *__restrict__ zbuf, int B, int d, int n_blk, int s
   }
 }
 
+// bf16 layers: the same blocks, quarters and tiles, on the bf16 matrix
+// instruction: z_i z_j = xs_i v_j (GramRows), v_j = fp32(xs_j sc) cut without
+// loss into three bf16 values (8 significant bits each, by truncation), so
+// that three v_mfma_f32_16x16x32_bf16 (exact products, fp32 sums) replace
+// eight fp32 ones of a sixteenth of their rate.
+// A step is 32 pairs: lane l loads, for the pairs 8 (l / 16) .. + 7, the
+// columns 4 (l % 16) .. + 3 of each side (8 bytes of a token row), and turns
+// the 8 x 4 values into one operand fragment (8 pairs of one column) per
+// column with byte permutes; v is formed and cut in registers (three stored
+// planes of v instead: 643 against 451 us, the row reads then bound it).
+// G's old values are read after the contraction: held across it (as in the fp32
+// kernel) they spill, 473 against 420 us per batch of 1024 OLMoE-shaped tokens
+// (1.6 GB of G moved, 3.8 TB/s; without the contraction 313).  The fp32
+// kernel took 548.
+// The two sides are not alike, so inside a diagonal 64 x 64 quarter the
+// elements above the diagonal are kept and mirrored, and the quarter below
+// the diagonal of a diagonal block is the mirror of the one above: G_u stays
+// exactly symmetric.
+__device__ __forceinline__ bf16x8 halves8(const u32x2 (&r)[8], int c) {
+  u32x4 f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    f[q] = __builtin_amdgcn_perm(r[2 * q + 1][c >> 1], r[2 * q][c >> 1],
+                                 (c & 1) ? 0x07060302u : 0x05040100u);
+  return __builtin_bit_cast(bf16x8, f);
+}
+
+__global__ __launch_bounds__(GM_WAVES * WAVE, 2)
+void k_calib_gram_bf16(GramRows gr, int B, int d, int n_blk, int slots_per_die,
+                       const int32_t *__restrict__ n_sel, const int32_t *__restrict__ sel_ids,
+                       const int32_t *__restrict__ offsets, const int32_t *__restrict__ pair_tok,
+                       float *__restrict__ G) {
+  const int x = blockIdx.x % N_XCD, i = blockIdx.x / N_XCD;
+  const int s = x + N_XCD * (i / n_blk);
+  int k = i % n_blk;
+  if (i / n_blk >= slots_per_die || s >= *n_sel) return;
+  const int p0 = offsets[s], p1 = offsets[s + 1];
+  if (p1 <= p0) return;
+  const int T = d / GM_TILE;
+  int I = 0;
+  while (k >= T - I) { k -= T - I; ++I; }
+  const int J = I + k;
+  const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+  const int m = lane & 15, kk = lane >> 4;
+  const int rb = I * GM_TILE + (w >> 1) * 64, cb = J * GM_TILE + (w & 1) * 64;
+  if (rb > cb) return;   // below the diagonal: the mirror of quarter 1
+  float *g = G + (size_t)sel_ids[s] * d * d;
+
+  // the tokens and scales of 64 pairs, one per lane (past the end: the zero row)
+  auto toks = [&](int pc) { return pc + lane < p1 ? pair_tok[pc + lane] : B; };
+  int tc = toks(p0), tn = toks(p0 + WAVE);
+  float scl = gr.sc[tc];
+  u32x2 ra[8], rv[8];
+  auto load = [&](int tv, int half) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint16_t *row = gr.xs + (uint32_t)__shfl(tv, 32 * half + 8 * kk + e) * (uint32_t)d;
+      ra[e] = *reinterpret_cast<const u32x2 *>(row + rb + 4 * m);
+      rv[e] = *reinterpret_cast<const u32x2 *>(row + cb + 4 * m);
+    }
+  };
+  load(tc, 0);
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int pc = p0; pc < p1; pc += WAVE) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half == 1 && pc + 32 >= p1) break;
+      float se[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) se[e] = __shfl(scl, 32 * half + 8 * kk + e);
+      bf16x8 fa[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) fa[a] = halves8(ra, a);
+      u32x2 cv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) cv[e] = rv[e];
+      // the next step's rows (past the last pair: the zero row)
+      if (half == 0) load(tc, 1);
+      else load(tn, 0);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        u32x4 fh, fm, fl;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[2], r1[2], r2[2];
+#pragma unroll
+          for (int z = 0; z < 2; ++z) {
+            const uint32_t wd = cv[2 * q + z][b >> 1];
+            v[z] = __uint_as_float((b & 1) ? (wd & 0xFFFF0000u) : (wd << 16)) * se[2 * q + z];
+            r1[z] = v[z] - __uint_as_float(__float_as_uint(v[z]) & 0xFFFF0000u);
+            r2[z] = r1[z] - __uint_as_float(__float_as_uint(r1[z]) & 0xFFFF0000u);
+          }
+          fh[q] = __builtin_amdgcn_perm(__float_as_uint(v[1]), __float_as_uint(v[0]), 0x07060302u);
+          fm[q] = __builtin_amdgcn_perm(__float_as_uint(r1[1]), __float_as_uint(r1[0]), 0x07060302u);
+          fl[q] = __builtin_amdgcn_perm(__float_as_uint(r2[1]), __float_as_uint(r2[0]), 0x07060302u);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          acc[a][b] = mfma_bf16_32(fa[a], __builtin_bit_cast(bf16x8, fl), acc[a][b]);
+          acc[a][b] = mfma_bf16_32(fa[a], __builtin_bit_cast(bf16x8, fm), acc[a][b]);
+          acc[a][b] = mfma_bf16_32(fa[a], __builtin_bit_cast(bf16x8, fh), acc[a][b]);
+        }
+      }
+    }
+    tc = tn;
+    scl = gr.sc[tc];
+    tn = toks(pc + 2 * WAVE);
+  }
+
+  // the block's old values (rows rb + 16 kk + 4 r + a, 16 bytes at cb + 4 m)
+  f32x4 old[4][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      old[r][a] = *(const f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m);
+
+  if (rb == cb) {
+    // a diagonal quarter: i <= j, mirrored
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int ii = 16 * kk + 4 * r + a, jj = 4 * m + b;
+          if (ii > jj) continue;
+          const float v = old[r][a][b] + acc[a][b][r];
+          g[(size_t)(rb + ii) * d + cb + jj] = v;
+          if (ii < jj) g[(size_t)(cb + jj) * d + rb + ii] = v;
+        }
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 v = old[r][a] + f32x4{acc[a][0][r], acc[a][1][r], acc[a][2][r], acc[a][3][r]};
+      *(f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m) = v;
+      old[r][a] = v;
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      *(f32x4 *)(g + (size_t)(cb + 4 * m + b) * d + rb + 16 * kk + 4 * r) =
+          f32x4{old[r][0][b], old[r][1][b], old[r][2][b], old[r][3][b]};
+}
+
 __global__ __launch_bounds__(CAL_THREADS)
 void k_fill_zero(uint32_t *__restrict__ p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)CAL_THREADS + threadIdx.x; i < n;
@@ -237,15 +527,26 @@ hipError_t launch_calib_stats(const void *x, bool bf16, int B, int d, int E, int
                               const int32_t *sel_ids, const int32_t *offsets,
                               const int32_t *pair_tok, double *inv, double *y, float *zbuf,
                               CalibStats st, hipStream_t s) {
-  launch_k(k_calib_norm, dim3(B), dim3(CAL_THREADS), 0, s, x, (int)bf16, B, d, inv, zbuf);
-  launch_k(k_calib_pairs, dim3(B * K), dim3(CAL_THREADS), 0, s, pairbuf, d, offsets, E, y);
-  launch_k(k_calib_moments, dim3(E, (d + CAL_THREADS - 1) / CAL_THREADS), dim3(CAL_THREADS), 0,
+  constexpr int per = CAL_THREADS / WAVE;
+  launch_k(k_calib_pairs, dim3((B * K + per - 1) / per), dim3(CAL_THREADS), 0, s,
+           pairbuf, d, offsets, E, y);
+  GramRows gr;
+  gr.z = zbuf;
+  gr.xs = reinterpret_cast<uint16_t *>(zbuf);
+  gr.sc = reinterpret_cast<float *>(gr.xs + (size_t)(B + 1) * d);
+  launch_k(k_calib_norm, dim3((B + per) / per), dim3(CAL_THREADS), 0, s, x, (int)bf16, B, d, inv,
+           gr);
+  launch_k(k_calib_moments, dim3(E, d / CM_COLS), dim3(CM_WAVES * WAVE), 0,
            s, x, (int)bf16, d, (const double *)inv, n_sel, sel_ids, offsets, pair_tok,
            (const double *)y, st);
   const int T = d / GM_TILE, n_blk = T * (T + 1) / 2;
   const int per_die = (E + N_XCD - 1) / N_XCD;
-  launch_k(k_calib_gram, dim3((unsigned)(N_XCD * per_die * n_blk)), dim3(GM_WAVES * WAVE), 0, s,
-           (const float *)zbuf, B, d, n_blk, per_die, n_sel, sel_ids, offsets, pair_tok, st.G);
+  const dim3 grid((unsigned)(N_XCD * per_die * n_blk));
+  if (bf16)
+    launch_k(k_calib_gram_bf16, grid, dim3(GM_WAVES * WAVE), 0, s, gr, B, d, n_blk, per_die, n_sel, sel_ids, offsets, pair_tok, st.G);
+  else
+    launch_k(k_calib_gram, grid, dim3(GM_WAVES * WAVE), 0, s, (const float *)zbuf, B, d, n_blk,
+             per_die, n_sel, sel_ids, offsets, pair_tok, st.G);
   return hipGetLastError();
 }
 

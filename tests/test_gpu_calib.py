@@ -206,3 +206,34 @@ def test_calibration_qwen3_shape(gu):
         a_scale = max(1e-6, float(np.max(np.abs(f["a"]))))
         assert np.max(np.abs(pa[u] - f["a"])) <= 1e-4 * a_scale, u
         assert abs(pb[u] - f["b"]) <= 1e-4 * max(1.0, abs(f["b"])), u
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -100, 1.0, 2.0 ** 60])
+@pytest.mark.parametrize("d,E,K,B", [(256, 4, 1, 33), (512, 6, 2, 97)])
+def test_gram_of_scaled_rows(gu, d, E, K, B, scale):
+    """bf16 layers: the Gram is that of unit rows whatever the scale of the
+    hidden states (a zero row and a few dominant entries among them), within
+    the fp32 sums' rounding (n pairs: n 2^-24 of each entry's bound 1, and
+    three roundings per product), exactly symmetric, and accumulates."""
+    from paper_2609_36222_amd import binding as bd
+    inp = W.custom_layer(d, E, K, 64, B, seed=61, zero_token=True)
+    z = inp["x"].copy()
+    z[1, 5] = 4096.0
+    z = z * np.float32(scale)
+    gl = gu.GpuLayer(inp)
+    x = gl.x(z)
+    stats = bd.calib_stats(gl.desc)
+    for _ in range(2):
+        bd.calib_accumulate(gl.desc, x, B, stats)
+    torch.cuda.synchronize()
+    head, _, _, G = read_stats(stats, E, d)
+    _, ids, _ = carith.route(z, inp["w_router"], inp["b_router"], K)
+    z64 = gu.to_np_f32(x).astype(np.float64)
+    nrm = np.linalg.norm(z64, axis=1, keepdims=True)
+    zb = np.divide(z64, nrm, out=np.zeros_like(z64), where=nrm > 0)
+    for u in range(E):
+        t = np.nonzero((ids == u).any(axis=1))[0]
+        assert int(head[u, 0]) == 2 * len(t)
+        ref = 2.0 * zb[t].T @ zb[t]
+        assert np.max(np.abs(G[u] - ref)) <= (len(t) + 3) * 2.0 ** -23, u
+        assert np.array_equal(G[u], G[u].T), u
