@@ -446,7 +446,7 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
                                  L->score_rule == BASE_SCORE_TOP1, flags, order, ex, den,
                                  at<float>(ws, o.scores), at<int32_t>(ws, o.counts), sel, nsel,
                                  slot, at<int32_t>(ws, o.exec_ids), at<float>(ws, o.exec_gates),
-                                 st));
+                                 device_cus(), st));
   stage_end(st);
   BASE_TRY(run_forward(L, x, B, logits, ids, sel, nsel, slot, bc, flags,
                        residual, y, ws, o, st, true));

@@ -183,7 +183,7 @@ hipError_t launch_select_backfill(int B, int K, int E, const int32_t *ids, const
                                   const float *ex, const float *den, float *scores,
                                   int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
                                   int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
-                                  hipStream_t st);
+                                  int n_cu, hipStream_t st);
 hipError_t launch_backfill(int B, int E, int K, int norm_topk, int flags,
                            const float *logits, const int32_t *ids,
                            const int32_t *slot_of, const int32_t *n_sel,

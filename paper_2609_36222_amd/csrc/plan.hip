@@ -234,8 +234,16 @@ void k_select(int B, int K, int E, const int32_t *__restrict__ ids,
 
 constexpr int BF_WAVES = 4;
 constexpr int SB_WAVES = SEL_THREADS / WAVE;   // wavefronts of k_select_backfill
-constexpr int SB_TOK = 2;                      // its tokens per workgroup (wavefronts 0 ..)
-static_assert(TOK_GROUP % SB_TOK == 0, "a token group in whole workgroups");
+// Tokens per workgroup of k_select_backfill (wavefronts 0 ..): two, doubled
+// until the workgroups, one per CU by their LDS, run in one round (E = 128, K =
+// 8, B = 1024: 30.6 us with two tokens in two rounds, 16.2 with four; below
+// the line no difference: B = 400 10.8 and 11.0).
+inline int sb_tokens(int B, int n_cu) {
+  int t = 2;
+  while (t < TOK_GROUP && (B + t - 1) / t > n_cu) t *= 2;
+  return t;
+}
+static_assert(TOK_GROUP <= SB_WAVES && TOK_GROUP % 2 == 0, "a token group in whole workgroups");
 
 // Per-wavefront LDS of the backfill
 template <int W>
@@ -385,7 +393,7 @@ void k_backfill(int B, int E, int K, int norm_topk, int flags,
 // execution order -- the values and the order of backfill_body.
 template <int NCH>
 __global__ __launch_bounds__(SEL_THREADS)
-void k_select_backfill(int B, int K, int E, const int32_t *__restrict__ ids,
+void k_select_backfill(int B, int K, int E, int sbt, const int32_t *__restrict__ ids,
                        const float *__restrict__ cost, int budget, int binary, int flags,
                        const uint8_t *__restrict__ order, const float *__restrict__ ex,
                        const float *__restrict__ den, float *__restrict__ scores,
@@ -396,12 +404,12 @@ void k_select_backfill(int B, int K, int E, const int32_t *__restrict__ ids,
   __shared__ int slot_s[MAX_E];
   const int lane = lane_id(), wv = wave_id();
   int tg, tq;
-  xcd_group(blockIdx.x, TOK_GROUP / SB_TOK, tg, tq);
+  xcd_group(blockIdx.x, TOK_GROUP / sbt, tg, tq);
   if (tg * TOK_GROUP >= B) return;
-  const bool active = wv < SB_TOK;
+  const bool active = wv < sbt;
   // the tokens of group tg sit on die tg % N_XCD, where k_tail wrote their
   // rank rows
-  const int t = tg * TOK_GROUP + tq * SB_TOK + wv, tc = min(t, B - 1);
+  const int t = tg * TOK_GROUP + tq * sbt + wv, tc = min(t, B - 1);
   int ov[NCH];
   float xv[NCH];
 #pragma unroll
@@ -964,10 +972,11 @@ hipError_t launch_select_backfill(int B, int K, int E, const int32_t *ids, const
                                   const float *ex, const float *den, float *scores,
                                   int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
                                   int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
-                                  hipStream_t st) {
-  const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP / SB_TOK));
+                                  int n_cu, hipStream_t st) {
+  const int sbt = sb_tokens(B, n_cu);
+  const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP / sbt));
 #define BASE_SB(C)                                                                         \
-  launch_k(k_select_backfill<C>, grid, dim3(SEL_THREADS), 0, st, B, K, E, ids, cost, budget, \
+  launch_k(k_select_backfill<C>, grid, dim3(SEL_THREADS), 0, st, B, K, E, sbt, ids, cost, budget, \
            (int)binary, flags, order, ex, den, scores, counts, sel_ids, n_sel, slot_of,     \
            exec_ids, exec_gates)
   if (E <= WAVE) BASE_SB(1);
