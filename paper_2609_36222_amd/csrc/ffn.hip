@@ -752,13 +752,43 @@ void k_down_split(int d, int I, int E, int kmax, int budget, const uint16_t *__r
   }
 }
 
-// fp32 experts (small layers): one wavefront per (kept slot, output row).
-// The lanes split the contraction (lane l takes elements l, l + 64, ..., so
-// every load of a row is contiguous across the wavefront) and each token's
-// dot product is summed across the lanes by the butterfly of
-// wave_tree_sum.  The slot's tokens are taken one after another; the row
-// stays in L1 between them.
-constexpr int F32_WAVES = 4;   // rows per workgroup
+// fp32 experts (small layers): one wavefront per (kept slot, two weight rows:
+// an output's gate and up row, or two rows of W_d).  Lane l takes the elements
+// 4 l .. 4 l + 3 of every 256 (16-byte loads) against eight token rows at a
+// time, and the 16 dot products are summed across the lanes together
+// (tree16).  These launches are latency: the slot's plan entries are
+// requested together, the weights before the token list has arrived.  (One
+// token after another with a six-step butterfly each: 9.4 and 15.2 us for
+// gate/up and down at d = 256, I = 512, six experts, B = 8; now 5.2 and 4.0;
+// at B = 64, 49.6 and 105.9 us, now 10.8 and 12.5.)
+constexpr int F32_WAVES = 4;   // wavefronts per workgroup
+constexpr int F32_TB = 8;      // token rows at a time
+
+// Lane 4 i .. 4 i + 3: row i / 8 (r0, r1) times token row i % 8 (tok[]), rows
+// of len elements.
+__device__ __forceinline__ float dots_2x8(const float *__restrict__ r0, const float *__restrict__ r1,
+                                          const float *const (&tok)[F32_TB], int len) {
+  const int lane = lane_id();
+  float v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = 0.0f;
+#pragma unroll 2
+  for (int k = 4 * lane; k < len; k += 4 * WAVE) {
+    float a[4], b[4], t[F32_TB][4];
+    load4(r0 + k, a);
+    load4(r1 + k, b);
+#pragma unroll
+    for (int j = 0; j < F32_TB; ++j) load4(tok[j] + k, t[j]);
+#pragma unroll
+    for (int j = 0; j < F32_TB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        v[j] = __builtin_fmaf(t[j][r], a[r], v[j]);
+        v[F32_TB + j] = __builtin_fmaf(t[j][r], b[r], v[F32_TB + j]);
+      }
+  }
+  return tree16(v);
+}
 
 __global__ __launch_bounds__(F32_WAVES * WAVE)
 void k_gateup_f32(const float *__restrict__ x, int d, int I, int E,
@@ -767,27 +797,19 @@ void k_gateup_f32(const float *__restrict__ x, int d, int I, int E,
                   const int32_t *__restrict__ n_sel_p,
                   const int32_t *__restrict__ offsets,
                   const int32_t *__restrict__ pair_tok, float *__restrict__ H) {
-  const int s = blockIdx.x;
-  if (s >= *n_sel_p) return;
-  const int u = sel_ids[s];
-  if (u < 0 || u >= E) return;   // only for a plan not made by base_select
-  const int p0 = offsets[s];
-  const int n = offsets[s + 1] - p0;
-  const int i = blockIdx.y * F32_WAVES + wave_id(), lane = lane_id();
+  const SpSlot sl = sp_slot(blockIdx.x, gridDim.x, 0, E, sel_ids, n_sel_p, offsets);
+  const int i = blockIdx.y * F32_WAVES + wave_id_u(), lane = lane_id();
   if (i >= I) return;
-  const float *wg = w13 + ((size_t)u * 2 * I + i) * d;
-  const float *wu = w13 + ((size_t)u * 2 * I + I + i) * d;
-  for (int tk = 0; tk < n; ++tk) {
-    const float *xr = x + (size_t)pair_tok[p0 + tk] * d;
-    float g = 0.0f, v = 0.0f;
-    for (int k = lane; k < d; k += WAVE) {
-      const float xv = xr[k];
-      g = __builtin_fmaf(xv, wg[k], g);
-      v = __builtin_fmaf(xv, wu[k], v);
-    }
-    g = wave_tree_sum(g);
-    v = wave_tree_sum(v);
-    if (lane == 0) H[(size_t)(p0 + tk) * I + i] = silu(g) * v;
+  const float *wg = w13 + ((size_t)sl.u * 2 * I + i) * d;
+  for (int c = 0; c < sl.n; c += F32_TB) {
+    const float *tok[F32_TB];
+#pragma unroll
+    for (int j = 0; j < F32_TB; ++j)
+      tok[j] = x + (size_t)pair_tok[sl.p0 + min(c + j, sl.n - 1)] * d;
+    const float g = dots_2x8(wg, wg + (size_t)I * d, tok, d);
+    const float u = xor_lane<32>(g);   // lanes 32 ..: the up row's
+    const int t = c + (lane >> 2);
+    if (lane < 32 && (lane & 3) == 0 && t < sl.n) H[(size_t)(sl.p0 + t) * I + i] = silu(g) * u;
   }
 }
 
@@ -798,21 +820,18 @@ void k_down_f32(int d, int I, int E, const float *__restrict__ w2,
                 const int32_t *__restrict__ offsets,
                 const float *__restrict__ pair_gate,
                 const float *__restrict__ H, float *__restrict__ pairbuf) {
-  const int s = blockIdx.x;
-  if (s >= *n_sel_p) return;
-  const int u = sel_ids[s];
-  if (u < 0 || u >= E) return;   // only for a plan not made by base_select
-  const int p0 = offsets[s];
-  const int n = offsets[s + 1] - p0;
-  const int c = blockIdx.y * F32_WAVES + wave_id(), lane = lane_id();
-  if (c >= d) return;
-  const float *wd = w2 + ((size_t)u * d + c) * I;
-  for (int tk = 0; tk < n; ++tk) {
-    const float *hr = H + (size_t)(p0 + tk) * I;
-    float o = 0.0f;
-    for (int k = lane; k < I; k += WAVE) o = __builtin_fmaf(hr[k], wd[k], o);
-    o = wave_tree_sum(o);
-    if (lane == 0) pairbuf[(size_t)(p0 + tk) * d + c] = pair_gate[p0 + tk] * o;
+  const SpSlot sl = sp_slot(blockIdx.x, gridDim.x, 0, E, sel_ids, n_sel_p, offsets);
+  const int r = 2 * (blockIdx.y * F32_WAVES + wave_id_u()), lane = lane_id();
+  if (r >= d) return;
+  const float *wd = w2 + ((size_t)sl.u * d + r) * I;
+  for (int c = 0; c < sl.n; c += F32_TB) {
+    const float *tok[F32_TB];
+#pragma unroll
+    for (int j = 0; j < F32_TB; ++j) tok[j] = H + (size_t)(sl.p0 + min(c + j, sl.n - 1)) * I;
+    const int t = c + ((lane >> 2) & 7), p = sl.p0 + min(t, sl.n - 1);
+    const float gt = pair_gate[p];
+    const float o = dots_2x8(wd, wd + I, tok, I);
+    if ((lane & 3) == 0 && t < sl.n) pairbuf[(size_t)p * d + r + (lane >> 5)] = gt * o;
   }
 }
 
@@ -916,7 +935,7 @@ hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K
              (const uint16_t *)w2,
              (const uint16_t *)w2s, hdr, units, pair_gate, (const uint16_t *)H, pairbuf);
   } else {
-    launch_k(k_down_f32, dim3(budget, (d + F32_WAVES - 1) / F32_WAVES),
+    launch_k(k_down_f32, dim3(budget, (d + 2 * F32_WAVES - 1) / (2 * F32_WAVES)),
                        dim3(F32_WAVES * WAVE), 0, st, d, I, E,
                        (const float *)w2, sel_ids, n_sel, offsets, pair_gate,
                        (const float *)H, pairbuf);

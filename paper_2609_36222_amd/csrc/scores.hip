@@ -37,36 +37,6 @@ constexpr int SC_PF = 2;                      // chunks requested ahead (registe
 static_assert(SC_T * SC_R == 16, "tree16 joins 16 dot products");
 static_assert(SC_TB == TOK_GROUP, "a workgroup's tokens are one group");
 
-// The halving trees of 16 dot products at once, v[i] holding lane j's
-// partial of dot i.  At the level of distance h the 2c values still held
-// are paired (i, i + c): a lane whose bit h is clear keeps dot i and sends
-// dot i + c, its partner (lane j ^ h) keeps i + c and sends i, and each adds
-// what it receives -- every lane then holds, for its dot, s[j] + s[j ^ h]
-// of that level.  After the levels 32, 16, 8, 4 lane j holds one dot,
-// number j / 4, and the levels 2 and 1 finish it in all four lanes of its
-// group.
-template <int C, int H>
-__device__ __forceinline__ void tree_level(float (&v)[16], int lane) {
-  const bool hi = (lane & H) != 0;
-#pragma unroll
-  for (int i = 0; i < C; ++i) {
-    const float keep = hi ? v[i + C] : v[i];
-    const float send = hi ? v[i] : v[i + C];
-    v[i] = keep + xor_lane<H>(send);
-  }
-}
-__device__ __forceinline__ float tree16(float (&v)[16]) {
-  const int lane = lane_id();
-  tree_level<8, 32>(v, lane);
-  tree_level<4, 16>(v, lane);
-  tree_level<2, 8>(v, lane);
-  tree_level<1, 4>(v, lane);
-  float s = v[0];
-  s = s + xor_lane<2>(s);
-  s = s + xor_lane<1>(s);
-  return s;
-}
-
 // Four consecutive elements of a token row as loaded (bf16 bits or fp32),
 // widened only where used, so that holding a request does not wait for it.
 template <typename XT> struct Raw4;

@@ -75,3 +75,17 @@ def test_kept_set_beyond_the_routes(gu):  # noqa: F811
     slot = np.full(40, -1, np.int32)
     slot[sel] = np.arange(30)
     _forward(gu, inp, logits, ids, sel, 30, slot, 30, 0)
+
+
+@pytest.mark.parametrize("B", [1, 8, 9, 33])
+@pytest.mark.parametrize("d,I", [(256, 64), (768, 320)])
+def test_fp32_rows(gu, B, d, I):  # noqa: F811
+    """fp32 layers: token batches of eight and their remainders, a row of I
+    shorter than a wavefront's pass and one with a remainder."""
+    run_case(gu, W.custom_layer(d, 6, 3, I, B, bf16=False, seed=80 + B), 4, flags=2)
+
+
+@pytest.mark.parametrize("B", [511, 513, 600])
+def test_selection_workgroups(gu, B):  # noqa: F811
+    """Where the fused selection takes more tokens per workgroup."""
+    run_case(gu, W.custom_layer(256, 24, 3, 64, B, seed=90), 7)
