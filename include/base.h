@@ -363,7 +363,8 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
  * base_select stage 2, base_moe_forward 3 to 8 (base_predict_cost runs the
  * tail kernel in its cost mode, untimed); base_decode_layer runs all of
  * them except that one
- * kernel makes the selection and the backfill: stage 2 times it and stage 3
+ * kernel makes the selection and the backfill (and, for batches of at most 64,
+ * or 32 when I > 2048, the compaction): stage 2 times it and stage 3 (and 4)
  * records its pair back to back.  The setting belongs
  * to the calling host thread; the caller keeps the events alive while it
  * is set.  Calls on a stream that is being captured ignore it (no event is

@@ -94,7 +94,7 @@ base_status check_ptr(const void *p, size_t a) {
 struct Layout {
   size_t logits, gdot, topk_ids, topk_w, cost, scores, counts, sel_ids, n_sel,
       slot_of, exec_ids, exec_gates, offsets, pair_tok, pair_gate, pair_of, order, ex,
-      den, hdr, units_gu, units_dn, tokoff, H, pairbuf, total;
+      den, hdr, units_gu, units_dn, tokoff, sprec, H, pairbuf, total;
 };
 
 size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -134,12 +134,14 @@ Layout layout(const base_layer *L, int32_t B, int32_t bc) {
   // the FFN's part tables and their header (bf16)
   const bool bf = L->dtype == BASE_BF16;
   // (one header per die; every die's run of units written on that die)
-  const size_t ug = bf ? (size_t)ffn_units_bound_gu(B, L->K, bc, ns, L->I) : 0;
-  const size_t ud = bf ? (size_t)ffn_units_bound_dn(B, L->K, bc, ns, L->d) : 0;
-  o.hdr = take(bf ? N_XCD * sizeof(FfnHdr) : 0);
+  const bool units = bf && !ffn_split(B, L->I), split = bf && ffn_split(B, L->I);
+  const size_t ug = units ? (size_t)ffn_units_bound_gu(B, L->K, bc, ns, L->I) : 0;
+  const size_t ud = units ? (size_t)ffn_units_bound_dn(B, L->K, bc, ns, L->d) : 0;
+  o.hdr = take(units ? N_XCD * sizeof(FfnHdr) : 0);
   o.units_gu = take(ug * sizeof(FfnUnit));
   o.units_dn = take(ud * sizeof(FfnUnit));
   o.tokoff = take(ug * FFN_GU_TOK * 4);
+  o.sprec = take(split ? N_XCD * ((size_t)bc + ns) * sizeof(SpRec) : 0);
   if (L->dtype == BASE_BF16) {
     // fragment-ordered SwiGLU activations (16-pair tiles)
     const size_t tiles = (size_t)ffn_max_tiles(B, L->K, bc, ns);
@@ -147,6 +149,8 @@ Layout layout(const base_layer *L, int32_t B, int32_t bc) {
   } else {
     o.H = take(BK * L->I * 4);
   }
+  // (small batches: gate/up's token lists, one per die, lie here until down
+  // writes its rows)
   o.pairbuf = take(P * L->d * 4);
   o.total = at;
   return o;
@@ -221,14 +225,15 @@ T *at(void *ws, size_t off) {
   return reinterpret_cast<T *>(static_cast<char *>(ws) + off);
 }
 
-// backfill (unless done with the selection) + compaction + FFN + combine,
-// on plan arrays already in place
+// backfill (unless done with the selection) + compaction (unless planned:
+// done with both) + FFN + combine, on plan arrays already in place
 base_status run_forward(const base_layer *L, const void *x, int32_t B,
                         const float *logits, const int32_t *ids,
                         const int32_t *sel_ids, const int32_t *n_sel,
                         const int32_t *slot_of, int32_t bc, int32_t flags,
                         const void *residual, void *y, void *ws,
-                        const Layout &o, hipStream_t st, bool backfilled = false) {
+                        const Layout &o, hipStream_t st, bool backfilled = false,
+                        bool planned = false) {
   const bool bf16 = L->dtype == BASE_BF16;
   int32_t *exec_ids = at<int32_t>(ws, o.exec_ids);
   float *exec_gates = at<float>(ws, o.exec_gates);
@@ -247,11 +252,14 @@ base_status run_forward(const base_layer *L, const void *x, int32_t B,
   FfnHdr *hdr = at<FfnHdr>(ws, o.hdr);
   FfnUnit *units_gu = at<FfnUnit>(ws, o.units_gu), *units_dn = at<FfnUnit>(ws, o.units_dn);
   uint32_t *tokoff = at<uint32_t>(ws, o.tokoff);
+  SpRec *rec = bf16 && ffn_split(B, L->I) ? at<SpRec>(ws, o.sprec) : nullptr;
+  int32_t *sptok = at<int32_t>(ws, o.pairbuf);
   // the same launch lists the FFN's parts and gate/up's token rows (bf16)
-  HIP_TRY(launch_compact(B, L->K, L->E, bc, ns, exec_ids, exec_gates, slot_of, n_sel,
-                         shared_gate(L) ? at<float>(ws, o.gdot) : nullptr, offsets,
-                         pair_tok, pair_gate, pair_of, sel_ids, bf16 && !ffn_split(B), L->d, L->I, tokoff,
-                         hdr, units_gu, units_dn, n_cu, st));
+  if (!planned)
+    HIP_TRY(launch_compact(B, L->K, L->E, bc, ns, exec_ids, exec_gates, slot_of, n_sel,
+                           shared_gate(L) ? at<float>(ws, o.gdot) : nullptr, offsets,
+                           pair_tok, pair_gate, pair_of, sel_ids, bf16 && !ffn_split(B, L->I), L->d, L->I, tokoff,
+                           hdr, units_gu, units_dn, rec, sptok, n_cu, st));
   stage_end(st);
   stage(5, st);   // no launch of its own: gate/up gathers its tokens itself
   stage_end(st);
@@ -262,11 +270,11 @@ base_status run_forward(const base_layer *L, const void *x, int32_t B,
   const int slots = backfilled ? std::min(bc, B * L->K) : bc;
   HIP_TRY(launch_gateup(bf16, packed, x, B, L->d, L->I, L->E, L->K, bc, slots, ns, L->w13,
                         L->w13_shared, sel_ids, n_sel, offsets, pair_tok, hdr, units_gu, n_cu,
-                        tokoff, at<void>(ws, o.H), st));
+                        tokoff, rec, sptok, at<void>(ws, o.H), st));
   stage_end(st);
   stage(7, st);
   HIP_TRY(launch_down(bf16, packed, B, L->d, L->I, L->E, L->K, bc, slots, ns, L->w2,
-                      L->w2_shared, sel_ids, n_sel, offsets, hdr, units_dn, n_cu, pair_gate,
+                      L->w2_shared, sel_ids, n_sel, offsets, hdr, units_dn, rec, n_cu, pair_gate,
                       at<void>(ws, o.H), at<float>(ws, o.pairbuf), st));
   stage_end(st);
   stage(8, st);
@@ -442,14 +450,24 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
                       L->pred_b, ids, w, cost, 3, L->score_rule, st, order, ex, den));
   stage_end(st);
   stage(2, st);   // selection and backfill in one launch
-  HIP_TRY(launch_select_backfill(B, L->K, L->E, ids, cost, bc,
-                                 L->score_rule == BASE_SCORE_TOP1, flags, order, ex, den,
-                                 at<float>(ws, o.scores), at<int32_t>(ws, o.counts), sel, nsel,
-                                 slot, at<int32_t>(ws, o.exec_ids), at<float>(ws, o.exec_gates),
-                                 device_cus(), st));
+  const bool split = ffn_split(B, L->I);   // ... and, for a small batch, the compaction
+  if (split)
+    HIP_TRY(launch_plan_split(
+        B, L->K, L->E, bc, L->n_shared, L->score_rule == BASE_SCORE_TOP1, flags, ids, cost, order,
+        ex, den, shared_gate(L) ? at<float>(ws, o.gdot) : nullptr, at<float>(ws, o.scores),
+        at<int32_t>(ws, o.counts), sel, nsel, slot, at<int32_t>(ws, o.exec_ids),
+        at<float>(ws, o.exec_gates), at<int32_t>(ws, o.offsets), at<int32_t>(ws, o.pair_tok),
+        at<float>(ws, o.pair_gate), at<int32_t>(ws, o.pair_of),
+        bf16 ? at<SpRec>(ws, o.sprec) : nullptr, at<int32_t>(ws, o.pairbuf), st));
+  else
+    HIP_TRY(launch_select_backfill(B, L->K, L->E, ids, cost, bc,
+                                   L->score_rule == BASE_SCORE_TOP1, flags, order, ex, den,
+                                   at<float>(ws, o.scores), at<int32_t>(ws, o.counts), sel, nsel,
+                                   slot, at<int32_t>(ws, o.exec_ids), at<float>(ws, o.exec_gates),
+                                   device_cus(), st));
   stage_end(st);
   BASE_TRY(run_forward(L, x, B, logits, ids, sel, nsel, slot, bc, flags,
-                       residual, y, ws, o, st, true));
+                       residual, y, ws, o, st, true, split));
   fill_plan(plan_out, ws, o, true);
   return BASE_OK;
 }
@@ -539,17 +557,19 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
   const int n_cu = device_cus();
   FfnHdr *hdr = at<FfnHdr>(ws, o.hdr);
   FfnUnit *units_gu = at<FfnUnit>(ws, o.units_gu), *units_dn = at<FfnUnit>(ws, o.units_dn);
+  SpRec *rec = bf16 && ffn_split(B, C.I) ? at<SpRec>(ws, o.sprec) : nullptr;
+  int32_t *sptok = at<int32_t>(ws, o.pairbuf);
   HIP_TRY(launch_compact(B, C.K, C.E, bc, 0, at<int32_t>(ws, o.exec_ids),
                          at<float>(ws, o.exec_gates), slot, nsel, nullptr, offsets, pair_tok,
                          at<float>(ws, o.pair_gate), at<int32_t>(ws, o.pair_of), sel,
-                         bf16 && !ffn_split(B), C.d, C.I, at<uint32_t>(ws, o.tokoff), hdr, units_gu, units_dn,
-                         n_cu, st));
+                         bf16 && !ffn_split(B, C.I), C.d, C.I, at<uint32_t>(ws, o.tokoff), hdr, units_gu, units_dn,
+                         rec, sptok, n_cu, st));
   const bool packed = C.w_layout == BASE_W_PACKED;
   HIP_TRY(launch_gateup(bf16, packed, z, B, C.d, C.I, C.E, C.K, bc, std::min(bc, B * C.K), 0, C.w13, nullptr, sel,
                         nsel, offsets, pair_tok, hdr, units_gu, n_cu, at<uint32_t>(ws, o.tokoff),
-                        at<void>(ws, o.H), st));
+                        rec, sptok, at<void>(ws, o.H), st));
   HIP_TRY(launch_down(bf16, packed, B, C.d, C.I, C.E, C.K, bc, std::min(bc, B * C.K), 0, C.w2, nullptr, sel, nsel,
-                      offsets, hdr, units_dn, n_cu, at<float>(ws, o.pair_gate),
+                      offsets, hdr, units_dn, rec, n_cu, at<float>(ws, o.pair_gate),
                       at<void>(ws, o.H), at<float>(ws, o.pairbuf), st));
   double *inv = at<double>(ws, o.total);
   double *y = at<double>(ws, o.total + up256((size_t)B * 8));

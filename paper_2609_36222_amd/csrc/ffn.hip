@@ -491,62 +491,92 @@ void k_down_bf16(int d, int I, int E, int ns, const uint16_t *__restrict__ w2r,
 static_assert(FFN_DN_PT == 8, "down tile-count cases");
 
 // ----------------------------------------------------------------------------
-// Small batches (ffn_split): every slot's pairs fit SP_NT 16-pair tiles, so a
-// row group's weights meet few tokens and the launch is a pure weight stream.
+// Small batches (ffn_split): every slot's pairs fit four 16-pair tiles, so a
+// row group's weights meet few tokens and the launch is a weight stream.
 // One workgroup per (slot, row group); its SP_WAVES wavefronts split the
-// contraction (wavefront s: the s-th contiguous share of the k-steps), each
+// contraction (wavefront w: the w-th contiguous share of the k-steps), each
 // with weights and token fragments of DW k-steps requested ahead into
 // registers, without a barrier until the shares are added through LDS in
 // ascending order.  The slot's expert, pairs and tokens come straight from
-// the plan arrays (no unit tables), the activations go out as rows
-// H[p][I].  A slot with more pairs than the tiles hold (only when routes
-// repeat an expert) takes several passes.
+// the die's copy of the slot records (no unit tables), the activations go out
+// as rows H[p][I].  A slot with more pairs than the tiles hold (only when
+// routes repeat an expert) takes several passes.
 // F weight fragments (16 rows each) by NT token tiles per wavefront.
-constexpr int SP_WAVES = 8;
-// Row-pair tiles per gate/up workgroup, row tiles per down workgroup (two
-// 16-token batches: the same weight tiles against two token tiles) and k-steps
-// in flight.  Two row-pair tiles are one 4 KiB block of the packed layout
-// per k-step and halve the token reads of one (gate/up at OLMoE's 134 MB, B =
-// 32: 25.7 against 28.2 us; equal below); down's launches at B <= 16 are
-// short of workgroups, so two row tiles (8.0 against 8.8 us at ten
-// Qwen3-shaped experts).  Six or eight k-steps ahead, or three at twice the
-// wavefronts per SIMD, measured the same or slower.
+// Row-pair tiles per gate/up workgroup, row tiles per down workgroup (at B <=
+// 16, above) and k-steps in flight.  Two row-pair tiles are one 4 KiB block of
+// the packed layout per k-step and halve the token reads of one (OLMoE-shaped
+// gate/up, 134 MB, B = 32: 25.7 against 28.2 us; equal below); down's launches
+// at B <= 16 are short of workgroups, so two row tiles (8.0 against 8.8 us at
+// ten Qwen3-shaped experts).  Four wavefronts, so that several workgroups of a
+// CU overlap one's sums with another's stream: eight measured equal at B = 1
+// and 16 and slower above (OLMoE-shaped down at B = 32 14.3 against 13.3,
+// Qwen3-shaped down at B = 64, 32 experts, 23.7 against 21.4, Mixtral-shaped
+// layer at B = 32 275 against 268).  Six or eight k-steps ahead, or three at
+// twice the wavefronts per SIMD, measured the same or slower.
+// Rates: Qwen3-shaped gate/up at B = 1 (50 MB) 18.0 -> 9.4 us, down (25 MB)
+// 8.8 -> 5.2; OLMoE-shaped at B = 32 26.0 -> 24.9 (5.4 TB/s) and 14.3 -> 13.3;
+// all 64 of its experts 92.3 -> 86.1 (6.2 TB/s) and 52.6 -> 44.3 (6.1 TB/s).
+constexpr int SP_WAVES = 4;
 constexpr int SPG_RT = 2, SPG_DW = 4;
 constexpr int SPD_RT1 = 2, SPD_RT2 = 4, SPD_DW = 4;
-constexpr int SP_NT = 2;   // token tiles per pass at most
-static_assert(16 * SP_NT >= FFN_SPLIT_B, "a slot's pairs in one pass");
+static_assert(FFN_SPLIT_B <= 4 * 16, "a slot's pairs in one pass");
 
-// slot y of the launch: its expert's matrix index, first pair and pair count
-// (n = 0: no such slot).  Slots kmax .. kmax + ns - 1 are the shared experts.
+// Slot y of the launch: kept slots 0 .. slots - 1, then the shared experts;
+// this workgroup's die's copy of the records.
 struct SpSlot {
   int u, p0, n;
-  bool shared;
 };
-__device__ __forceinline__ SpSlot sp_slot(int s, int kmax, int budget, int E,
-                                          const int32_t *__restrict__ sel_ids,
-                                          const int32_t *__restrict__ n_sel_p,
-                                          const int32_t *__restrict__ offsets) {
-  const bool sh = s >= kmax;
-  const int o = sh ? budget + (s - kmax) : s;
-  // all requested together
-  const int u = sel_ids[sh ? 0 : s], a = offsets[o], b = offsets[o + 1], ns = *n_sel_p;
-  SpSlot r;
-  r.shared = sh;
-  r.u = __builtin_amdgcn_readfirstlane(sh ? s - kmax : u);
-  r.p0 = __builtin_amdgcn_readfirstlane(a);
-  r.n = __builtin_amdgcn_readfirstlane(b - a);
-  if (!sh && (s >= ns || u < 0 || u >= E)) r.n = 0;   // u: only for a plan not made by base_select
-  return r;
+__device__ __forceinline__ int sp_die() { return (blockIdx.x + gridDim.x * blockIdx.y) % N_XCD; }
+__device__ __forceinline__ SpSlot sp_slot(int slots, int budget, int nrec,
+                                          const SpRec *__restrict__ rec) {
+  const int s = blockIdx.y;
+  const SpRec r = rec[sp_die() * nrec + (s < slots ? s : budget + (s - slots))];
+  return {__builtin_amdgcn_readfirstlane(r.u), __builtin_amdgcn_readfirstlane(r.p0),
+          __builtin_amdgcn_readfirstlane(r.n)};
 }
 
 // first k-step of wavefront w's share of KS
 __device__ __forceinline__ int sp_share(int KS, int w) { return w * KS / SP_WAVES; }
 
+// Row-major weights.  The MFMA operand has its 16 rows in consecutive lanes and
+// a row's four 16-byte pieces 16 lanes apart; loaded that way every four lanes
+// touch four lines, and the load path, which takes four lanes' 64 bytes at a
+// time, moved 4.0 TB/s (Qwen1.5-MoE-shaped gate/up, B = 61: 63 us).  So lane
+// l loads piece l % 4 of row l / 4 of weights and token rows alike, and each
+// fragment is put into operand order through 1 KiB of the wavefront's own
+// LDS: piece (g, m) at 16 g + (m ^ 2 g), so that neither side of the exchange
+// meets a bank twice: 55.9 us; down 37.6 -> 32.6; the layer at B = 31 111 ->
+// 103, at B = 8 91 (120 with the unit kernels).
+__device__ __forceinline__ int sp_put(int lane) {   // this lane's piece, in 16-byte units
+  const int m = lane >> 2, g = lane & 3;
+  return 16 * g + (m ^ (2 * g));
+}
+__device__ __forceinline__ int sp_get(int lane) {
+  const int m = lane & 15, g = lane >> 4;
+  return 16 * g + (m ^ (2 * g));
+}
+// Row and piece of a fragment that this lane loads.
+template <bool PACKED>
+__device__ __forceinline__ int sp_row(int lane) { return PACKED ? lane & 15 : lane >> 2; }
+template <bool PACKED>
+__device__ __forceinline__ uint32_t sp_piece(int lane) {
+  return 16u * (uint32_t)(PACKED ? lane >> 4 : lane & 3);
+}
+// LDS of one wavefront, in KiB: its partial sums, or (row-major) before them
+// the fragments in exchange.
+template <int F, int NT, bool PACKED>
+constexpr int sp_kib() {
+  return PACKED || F * NT > F + NT ? F * NT : F + NT;
+}
+
 // acc[f][j] += sum over this wavefront's k-steps [k0, k1) of fragment f of
-// the weights times token tile j; lw / lt: the byte offsets of k-step ks.
-template <int F, int NT, int DW, typename LW, typename LT>
-__device__ __forceinline__ void sp_stream(int k0, int k1, LW lw, LT lt, f32x4 (&acc)[F][NT]) {
+// the weights times token tile j; lw / lt: the loads of k-step ks; sh: the
+// wavefront's LDS.
+template <int F, int NT, int DW, bool PACKED, typename LW, typename LT>
+__device__ __forceinline__ void sp_stream(int k0, int k1, LW lw, LT lt, f32x4 *sh,
+                                          f32x4 (&acc)[F][NT]) {
   bf16x8 w[DW][F], t[DW][NT];
+  const int lane = lane_id();
   auto request = [&](int p, int ks) {
 #pragma unroll
     for (int f = 0; f < F; ++f) w[p][f] = lw(f, ks);
@@ -554,6 +584,17 @@ __device__ __forceinline__ void sp_stream(int k0, int k1, LW lw, LT lt, f32x4 (&
     for (int j = 0; j < NT; ++j) t[p][j] = lt(j, ks);
   };
   auto use = [&](int p) {
+    if constexpr (!PACKED) {
+      bf16x8 *x = reinterpret_cast<bf16x8 *>(sh);
+#pragma unroll
+      for (int f = 0; f < F; ++f) x[f * WAVE + sp_put(lane)] = w[p][f];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) x[(F + j) * WAVE + sp_put(lane)] = t[p][j];
+#pragma unroll
+      for (int f = 0; f < F; ++f) w[p][f] = x[f * WAVE + sp_get(lane)];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) t[p][j] = x[(F + j) * WAVE + sp_get(lane)];
+    }
 #pragma unroll
     for (int f = 0; f < F; ++f)
 #pragma unroll
@@ -584,7 +625,7 @@ __device__ __forceinline__ void sp_tiles(int nt, Fn f) {
   f(std::integral_constant<int, NT>{});
 }
 
-template <int NT, int RT, bool PACKED>
+template <int NT, int RT, bool PACKED, int KIB>
 __device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uint16_t *w13,
                                              int rp0, rsrc_t rx, const uint32_t (&tv)[NT], int n,
                                              uint16_t *__restrict__ h0) {
@@ -606,7 +647,7 @@ __device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uin
     const uint32_t tb = (uint32_t)(RT * 16 * d * 2);
     rg = make_rsrc(w13 + (size_t)16 * rp0 * d, tb);
     ru = make_rsrc(w13 + (size_t)(I + 16 * rp0) * d, tb);
-    v0 = (uint32_t)(lane & 15) * (uint32_t)(d * 2) + (uint32_t)(lane >> 4) * 16u;
+    v0 = (uint32_t)sp_row<PACKED>(lane) * (uint32_t)(d * 2) + sp_piece<PACKED>(lane);
   }
   auto lw = [&](int f, int ks) {
     const uint32_t o = ks < k1 ? (uint32_t)ks * (PACKED ? 4096u : 64u) : FFN_TOK_PAD;
@@ -617,11 +658,11 @@ __device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uin
   auto lt = [&](int j, int ks) {
     return bload(rx, ks < k1 ? tv[j] + (uint32_t)ks * 64u : FFN_TOK_PAD, 0);
   };
-  sp_stream<F, NT, SPG_DW>(k0, k1, lw, lt, acc);
+  sp_stream<F, NT, SPG_DW, PACKED>(k0, k1, lw, lt, red + w * KIB * WAVE, acc);
 #pragma unroll
   for (int f = 0; f < F; ++f)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) red[(w * F * NT + f * NT + j) * WAVE + lane] = acc[f][j];
+    for (int j = 0; j < NT; ++j) red[(w * KIB + f * NT + j) * WAVE + lane] = acc[f][j];
   __syncthreads();
   // (row-pair tile, token tile, half of the lane's four rows) in turn
   for (int it = w; it < 2 * RT * NT; it += SP_WAVES) {
@@ -630,8 +671,8 @@ __device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uin
     float g0 = 0.0f, g1 = 0.0f, u0 = 0.0f, u1 = 0.0f;
 #pragma unroll
     for (int s = 0; s < SP_WAVES; ++s) {
-      const float2 a = *reinterpret_cast<const float2 *>(rf + (s * F * NT + i * NT + j) * WAVE * 4);
-      const float2 b = *reinterpret_cast<const float2 *>(rf + (s * F * NT + (RT + i) * NT + j) * WAVE * 4);
+      const float2 a = *reinterpret_cast<const float2 *>(rf + (s * KIB + i * NT + j) * WAVE * 4);
+      const float2 b = *reinterpret_cast<const float2 *>(rf + (s * KIB + (RT + i) * NT + j) * WAVE * 4);
       g0 = g0 + a.x; g1 = g1 + a.y;
       u0 = u0 + b.x; u1 = u1 + b.y;
     }
@@ -644,27 +685,29 @@ __device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uin
   }
 }
 
-// NT: token tiles per pass (1 or 2); RT row-pair tiles per workgroup
+// NT: token tiles per pass (1, 2 or 4); RT row-pair tiles per workgroup
 template <int NT, int RT, bool PACKED>
 __global__ __launch_bounds__(SP_WAVES * WAVE)
-void k_gateup_split(int d, int I, int E, int kmax, int budget, const uint16_t *__restrict__ w13r,
-                    const uint16_t *__restrict__ w13s, const int32_t *__restrict__ sel_ids,
-                    const int32_t *__restrict__ n_sel, const int32_t *__restrict__ offsets,
-                    const int32_t *__restrict__ pair_tok, const uint16_t *__restrict__ x, int B,
-                    uint16_t *__restrict__ H) {
-  __shared__ f32x4 red[SP_WAVES * 2 * RT * NT * WAVE];
-  const SpSlot sl = sp_slot(blockIdx.y, kmax, budget, E, sel_ids, n_sel, offsets);
+void k_gateup_split(int d, int I, int E, int slots, int budget, int nrec, int np,
+                    const uint16_t *__restrict__ w13r, const uint16_t *__restrict__ w13s,
+                    const SpRec *__restrict__ rec, const int32_t *__restrict__ sptok,
+                    const uint16_t *__restrict__ x, int B, uint16_t *__restrict__ H) {
+  constexpr int KIB = sp_kib<2 * RT, NT, PACKED>();
+  __shared__ f32x4 red[SP_WAVES * KIB * WAVE];
+  const SpSlot sl = sp_slot(slots, budget, nrec, rec);
+  const int32_t *tok = sptok + (size_t)sp_die() * np + sl.p0;
   const int lane = lane_id(), rp0 = blockIdx.x * RT;
-  const uint16_t *w13 = (sl.shared ? w13s : w13r) + (size_t)sl.u * 2 * I * d;
+  const uint16_t *w13 = sl.u < E ? w13r + (size_t)sl.u * 2 * I * d
+                                 : w13s + (size_t)(sl.u - E) * 2 * I * d;
   const rsrc_t rx = make_rsrc(x, (uint32_t)B * (uint32_t)d * 2u);
   for (int c = 0; c < sl.n; c += 16 * NT) {
     const int n = min(sl.n - c, 16 * NT);
     uint32_t tv[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const int i = 16 * j + (lane & 15);
-      const int t = pair_tok[sl.p0 + c + min(i, n - 1)];
-      tv[j] = i < n ? (uint32_t)t * (uint32_t)d * 2u + (uint32_t)(lane >> 4) * 16u : FFN_TOK_PAD;
+      const int i = 16 * j + sp_row<PACKED>(lane);
+      const int t = tok[c + min(i, n - 1)];
+      tv[j] = i < n ? (uint32_t)t * (uint32_t)d * 2u + sp_piece<PACKED>(lane) : FFN_TOK_PAD;
     }
     if (c > 0) __syncthreads();
     uint16_t *h0 = H + (size_t)(sl.p0 + c) * I;
@@ -673,12 +716,12 @@ void k_gateup_split(int d, int I, int E, int kmax, int budget, const uint16_t *_
       uint32_t t[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) t[j] = tv[j];
-      gateup_split<N, RT, PACKED>(red, d, I, w13, rp0, rx, t, n, h0);
+      gateup_split<N, RT, PACKED, KIB>(red, d, I, w13, rp0, rx, t, n, h0);
     });
   }
 }
 
-template <int NT, int RT, bool PACKED>
+template <int NT, int RT, bool PACKED, int KIB>
 __device__ __forceinline__ void down_split(f32x4 *red, int d, int I, const uint16_t *w2, int rt0,
                                            const uint16_t *__restrict__ h0, int n,
                                            const float *__restrict__ gate0,
@@ -698,10 +741,10 @@ __device__ __forceinline__ void down_split(f32x4 *red, int d, int I, const uint1
     v0 = lane * 16 + (rt0 & 3) * 1024;
   } else {
     rw = make_rsrc(w2 + (size_t)16 * rt0 * I, (uint32_t)(RT * 16 * I * 2));
-    v0 = (uint32_t)(lane & 15) * (uint32_t)(I * 2) + (uint32_t)(lane >> 4) * 16u;
+    v0 = (uint32_t)sp_row<PACKED>(lane) * (uint32_t)(I * 2) + sp_piece<PACKED>(lane);
   }
   const rsrc_t rt = make_rsrc(h0, (uint32_t)n * (uint32_t)I * 2u);
-  const uint32_t hv = (uint32_t)(lane & 15) * (uint32_t)(I * 2) + (uint32_t)(lane >> 4) * 16u;
+  const uint32_t hv = (uint32_t)sp_row<PACKED>(lane) * (uint32_t)(I * 2) + sp_piece<PACKED>(lane);
   auto lw = [&](int f, int ks) {
     const uint32_t o = ks < k1 ? (uint32_t)ks * (PACKED ? 4096u : 64u) : FFN_TOK_PAD;
     return bload(rw, v0 + (PACKED ? (uint32_t)f * 1024u : (uint32_t)f * (uint32_t)(16 * I * 2)) + o, 0);
@@ -710,18 +753,18 @@ __device__ __forceinline__ void down_split(f32x4 *red, int d, int I, const uint1
     return bload(rt, ks < k1 ? hv + (uint32_t)j * (uint32_t)(16 * I * 2) + (uint32_t)ks * 64u
                              : FFN_TOK_PAD, 0);
   };
-  sp_stream<RT, NT, SPD_DW>(k0, k1, lw, lt, acc);
+  sp_stream<RT, NT, SPD_DW, PACKED>(k0, k1, lw, lt, red + w * KIB * WAVE, acc);
 #pragma unroll
   for (int f = 0; f < RT; ++f)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) red[(w * RT * NT + f * NT + j) * WAVE + lane] = acc[f][j];
+    for (int j = 0; j < NT; ++j) red[(w * KIB + f * NT + j) * WAVE + lane] = acc[f][j];
   __syncthreads();
   for (int it = w; it < RT * NT; it += SP_WAVES) {
     const int f = it / NT, j = it % NT, tk = 16 * j + (lane & 15);
     f32x4 o = red[it * WAVE + lane];
 #pragma unroll
     for (int s = 1; s < SP_WAVES; ++s) {
-      const f32x4 a = red[(s * RT * NT + it) * WAVE + lane];
+      const f32x4 a = red[(s * KIB + it) * WAVE + lane];
       o[0] = o[0] + a[0]; o[1] = o[1] + a[1]; o[2] = o[2] + a[2]; o[3] = o[3] + a[3];
     }
     if (tk < n) {
@@ -734,19 +777,19 @@ __device__ __forceinline__ void down_split(f32x4 *red, int d, int I, const uint1
 
 template <int NT, int RT, bool PACKED>
 __global__ __launch_bounds__(SP_WAVES * WAVE)
-void k_down_split(int d, int I, int E, int kmax, int budget, const uint16_t *__restrict__ w2r,
-                  const uint16_t *__restrict__ w2s, const int32_t *__restrict__ sel_ids,
-                  const int32_t *__restrict__ n_sel, const int32_t *__restrict__ offsets,
-                  const float *__restrict__ pair_gate, const uint16_t *__restrict__ H,
+void k_down_split(int d, int I, int E, int slots, int budget, int nrec,
+                  const uint16_t *__restrict__ w2r, const uint16_t *__restrict__ w2s,
+                  const SpRec *__restrict__ rec, const float *__restrict__ pair_gate, const uint16_t *__restrict__ H,
                   float *__restrict__ pairbuf) {
-  __shared__ f32x4 red[SP_WAVES * RT * NT * WAVE];
-  const SpSlot sl = sp_slot(blockIdx.y, kmax, budget, E, sel_ids, n_sel, offsets);
-  const uint16_t *w2 = (sl.shared ? w2s : w2r) + (size_t)sl.u * d * I;
+  constexpr int KIB = sp_kib<RT, NT, PACKED>();
+  __shared__ f32x4 red[SP_WAVES * KIB * WAVE];
+  const SpSlot sl = sp_slot(slots, budget, nrec, rec);
+  const uint16_t *w2 = sl.u < E ? w2r + (size_t)sl.u * d * I : w2s + (size_t)(sl.u - E) * d * I;
   for (int c = 0; c < sl.n; c += 16 * NT) {
     const int n = min(sl.n - c, 16 * NT), p0 = sl.p0 + c, rt0 = blockIdx.x * RT;
     if (c > 0) __syncthreads();
     sp_tiles<NT>((n + 15) / 16, [&](auto k) {
-      down_split<decltype(k)::value, RT, PACKED>(red, d, I, w2, rt0, H + (size_t)p0 * I, n,
+      down_split<decltype(k)::value, RT, PACKED, KIB>(red, d, I, w2, rt0, H + (size_t)p0 * I, n,
                                                  pair_gate + p0, pairbuf + (size_t)p0 * d);
     });
   }
@@ -761,6 +804,22 @@ void k_down_split(int d, int I, int E, int kmax, int budget, const uint16_t *__r
 // token after another with a six-step butterfly each: 9.4 and 15.2 us for
 // gate/up and down at d = 256, I = 512, six experts, B = 8; now 5.2 and 4.0;
 // at B = 64, 49.6 and 105.9 us, now 10.8 and 12.5.)
+struct F32Slot {
+  int u, p0, n;
+};
+__device__ __forceinline__ F32Slot f32_slot(int E, const int32_t *__restrict__ sel_ids,
+                                            const int32_t *__restrict__ n_sel_p,
+                                            const int32_t *__restrict__ offsets) {
+  const int s = blockIdx.x;
+  // all requested together
+  const int u = sel_ids[s], a = offsets[s], b = offsets[s + 1], ns = *n_sel_p;
+  F32Slot r;
+  r.u = __builtin_amdgcn_readfirstlane(u);
+  r.p0 = __builtin_amdgcn_readfirstlane(a);
+  r.n = __builtin_amdgcn_readfirstlane(b - a);
+  if (s >= ns || u < 0 || u >= E) r.n = 0;   // u: only for a plan not made by base_select
+  return r;
+}
 constexpr int F32_WAVES = 4;   // wavefronts per workgroup
 constexpr int F32_TB = 8;      // token rows at a time
 
@@ -797,7 +856,7 @@ void k_gateup_f32(const float *__restrict__ x, int d, int I, int E,
                   const int32_t *__restrict__ n_sel_p,
                   const int32_t *__restrict__ offsets,
                   const int32_t *__restrict__ pair_tok, float *__restrict__ H) {
-  const SpSlot sl = sp_slot(blockIdx.x, gridDim.x, 0, E, sel_ids, n_sel_p, offsets);
+  const F32Slot sl = f32_slot(E, sel_ids, n_sel_p, offsets);
   const int i = blockIdx.y * F32_WAVES + wave_id_u(), lane = lane_id();
   if (i >= I) return;
   const float *wg = w13 + ((size_t)sl.u * 2 * I + i) * d;
@@ -820,7 +879,7 @@ void k_down_f32(int d, int I, int E, const float *__restrict__ w2,
                 const int32_t *__restrict__ offsets,
                 const float *__restrict__ pair_gate,
                 const float *__restrict__ H, float *__restrict__ pairbuf) {
-  const SpSlot sl = sp_slot(blockIdx.x, gridDim.x, 0, E, sel_ids, n_sel_p, offsets);
+  const F32Slot sl = f32_slot(E, sel_ids, n_sel_p, offsets);
   const int r = 2 * (blockIdx.y * F32_WAVES + wave_id_u()), lane = lane_id();
   if (r >= d) return;
   const float *wd = w2 + ((size_t)sl.u * d + r) * I;
@@ -884,16 +943,18 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
                          const void *w13s, const int32_t *sel_ids, const int32_t *n_sel,
                          const int32_t *offsets, const int32_t *pair_tok,
                          const FfnHdr *hdr, const FfnUnit *units, int n_cu,
-                         const uint32_t *tokoff, void *H, hipStream_t st) {
-  if (bf16 && ffn_split(B)) {
+                         const uint32_t *tokoff, const SpRec *rec, const int32_t *sptok, void *H,
+                         hipStream_t st) {
+  if (bf16 && ffn_split(B, I)) {
     const dim3 grid(I / 16 / SPG_RT, slots + ns);
 #define BASE_GS(N, P) k_gateup_split<N, SPG_RT, P>
-    const auto kern = B <= 16 ? (packed ? BASE_GS(1, true) : BASE_GS(1, false))
-                              : (packed ? BASE_GS(2, true) : BASE_GS(2, false));
+    const auto kern = B <= 16   ? (packed ? BASE_GS(1, true) : BASE_GS(1, false))
+                      : B <= 32 ? (packed ? BASE_GS(2, true) : BASE_GS(2, false))
+                                : (packed ? BASE_GS(4, true) : BASE_GS(4, false));
 #undef BASE_GS
-    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, (const uint16_t *)w13,
-             (const uint16_t *)w13s, sel_ids, n_sel, offsets, pair_tok, (const uint16_t *)x, B,
-             (uint16_t *)H);
+    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, budget + ns,
+             B * (K + ns), (const uint16_t *)w13, (const uint16_t *)w13s, rec, sptok,
+             (const uint16_t *)x, B, (uint16_t *)H);
   } else if (bf16) {
     launch_k(packed ? k_gateup_bf16<true> : k_gateup_bf16<false>, dim3(ffn_gu_grid(n_cu)),
              dim3(FFN_WAVES * WAVE), 0, st, d, I, E, ns, (const uint16_t *)w13,
@@ -911,17 +972,17 @@ hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K
                        int budget, int slots, int ns, const void *w2, const void *w2s,
                        const int32_t *sel_ids,
                        const int32_t *n_sel, const int32_t *offsets,
-                       const FfnHdr *hdr, const FfnUnit *units, int n_cu,
+                       const FfnHdr *hdr, const FfnUnit *units, const SpRec *rec, int n_cu,
                        const float *pair_gate, const void *H, float *pairbuf, hipStream_t st) {
-  if (bf16 && ffn_split(B)) {
+  if (bf16 && ffn_split(B, I)) {
     const dim3 grid(d / 16 / (B <= 16 ? SPD_RT1 : SPD_RT2), slots + ns);
 #define BASE_DS(N, R, P) k_down_split<N, R, P>
-    const auto kern = B <= 16 ? (packed ? BASE_DS(1, SPD_RT1, true) : BASE_DS(1, SPD_RT1, false))
-                              : (packed ? BASE_DS(2, SPD_RT2, true) : BASE_DS(2, SPD_RT2, false));
+    const auto kern = B <= 16   ? (packed ? BASE_DS(1, SPD_RT1, true) : BASE_DS(1, SPD_RT1, false))
+                      : B <= 32 ? (packed ? BASE_DS(2, SPD_RT2, true) : BASE_DS(2, SPD_RT2, false))
+                                : (packed ? BASE_DS(4, SPD_RT2, true) : BASE_DS(4, SPD_RT2, false));
 #undef BASE_DS
-    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, (const uint16_t *)w2,
-             (const uint16_t *)w2s, sel_ids, n_sel, offsets, pair_gate, (const uint16_t *)H,
-             pairbuf);
+    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, budget + ns,
+             (const uint16_t *)w2, (const uint16_t *)w2s, rec, pair_gate, (const uint16_t *)H, pairbuf);
   } else if (bf16) {
     const int kind = ffn_dn_kind(budget, ns, I);
     const auto kern =

@@ -104,15 +104,30 @@ constexpr uint32_t FFN_TOK_PAD = 0x80000000u;   // past every x: a buffer load r
 static_assert(FFN_GU_PT <= FFN_WAVES, "one token tile per gate/up wavefront");
 static_assert((size_t)MAX_B * 16384 * 2 < FFN_TOK_PAD, "token row offsets below the pad mark");
 
-// Batches of at most FFN_SPLIT_B tokens take the FFN's split kernels (see
-// "Small batches" in ffn.hip), which need no unit tables: a slot then holds
-// at most two 16-pair tiles, and the launch is a weight stream.  Measured per
-// layer against the unit kernels: qwen3-shaped B = 1 59 -> 44 us, B = 16 64 ->
-// 51, OLMoE-shaped B = 32 76 -> 71, Mixtral-shaped B = 16 295 -> 274; with
-// four tiles per slot (B = 64) they are equal or slower (Mixtral-shaped 295
-// -> 306), their token reads then exceeding the weights'.
-constexpr int FFN_SPLIT_B = 32;
-__host__ __device__ inline bool ffn_split(int B) { return B <= FFN_SPLIT_B; }
+// Batches of at most FFN_SPLIT_B tokens (FFN_SPLIT_LONG_B when down's
+// contraction is long) take the FFN's split kernels (see "Small batches" in
+// ffn.hip), which need no unit tables, and the fused layer makes their plan in
+// one launch (k_plan_split).  A slot then holds at most four 16-pair tiles and
+// the FFN is a weight stream.  Measured per layer against the unit kernels and
+// two plan launches (us): Qwen3-shaped, ten kept experts, B = 1 60 -> 38, B = 16
+// 65 -> 45, B = 48 67 -> 54; 32 kept, B = 64 95 -> 87; OLMoE-shaped B = 32 76 ->
+// 63, B = 64 79 -> 71; row-major Qwen1.5-MoE-shaped B = 31 120 -> 103, B = 61
+// 127 -> 115; Mixtral-shaped B = 32 295 -> 268, but at B = 64 295 -> 300 (its
+// gate/up, with 32 pairs a slot, reads as many token bytes as weights).
+// Beyond 64 the token reads exceed the weights'.
+constexpr int FFN_SPLIT_B = 64, FFN_SPLIT_LONG_B = 32;
+__host__ __device__ inline bool ffn_split(int B, int I) {
+  return B <= (ffn_dn_long(I) ? FFN_SPLIT_LONG_B : FFN_SPLIT_B);
+}
+
+// Slot s of a small batch for the split kernels, one copy per die (written by
+// the plan's workgroup on that die, so that the FFN's first loads hit that
+// die's L2): expert u (u >= E: shared expert u - E), first pair and pair count
+// (0: nothing kept).  Records 0 .. budget - 1 are the kept slots, budget + i
+// shared expert i; the die's copy of the pair list's tokens lies beside it.
+struct alignas(16) SpRec {
+  int32_t u, p0, n, pad;
+};
 
 // A unit: expert u (u >= E: shared expert u - E), the part's first 16-pair
 // tile, its tile count, its first pair in the compacted order and its pair
@@ -184,6 +199,16 @@ hipError_t launch_select_backfill(int B, int K, int E, const int32_t *ids, const
                                   int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
                                   int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
                                   int n_cu, hipStream_t st);
+// selection, backfill and compaction in one launch, for ffn_split batches
+// (same results as the three); rec / sptok (bf16 layers, else null): the split
+// kernels' records and token lists
+hipError_t launch_plan_split(int B, int K, int E, int budget, int ns, bool binary, int flags,
+                             const int32_t *ids, const float *cost, const uint8_t *order,
+                             const float *ex, const float *den, const float *gdot,
+                             float *scores, int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
+                             int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
+                             int32_t *offsets, int32_t *pair_tok, float *pair_gate,
+                             int32_t *pair_of, SpRec *rec, int32_t *sptok, hipStream_t st);
 hipError_t launch_backfill(int B, int E, int K, int norm_topk, int flags,
                            const float *logits, const int32_t *ids,
                            const int32_t *slot_of, const int32_t *n_sel,
@@ -195,14 +220,15 @@ hipError_t launch_backfill(int B, int E, int K, int norm_topk, int flags,
 // at most ffn_units_bound_gu / _dn rows), the per-die headers and gate/up's
 // token row offsets (tokoff, FFN_GU_TOK per gate/up unit; d: the hidden
 // size); n_cu: the device's compute units (the FFN launches' sizes follow
-// from it).
+// from it).  Without tables, rec / sptok (may be null) as launch_plan_split.
 hipError_t launch_compact(int B, int K, int E, int budget, int ns, const int32_t *exec_ids,
                           const float *exec_gates, const int32_t *slot_of,
                           const int32_t *n_sel, const float *gdot, int32_t *offsets,
                           int32_t *pair_tok, float *pair_gate,
                           int32_t *pair_of, const int32_t *sel_ids, bool tables, int d,
                           int I, uint32_t *tokoff, FfnHdr *hdr, FfnUnit *units_gu,
-                          FfnUnit *units_dn, int n_cu, hipStream_t st);
+                          FfnUnit *units_dn, SpRec *rec, int32_t *sptok, int n_cu,
+                          hipStream_t st);
 hipError_t launch_pack(const void *w13, const void *w2, void *w13p, void *w2p,
                        int E, int d, int I, hipStream_t st);
 // slots: at most this many kept slots (budget, or fewer where the kept set is
@@ -214,12 +240,13 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
                          const int32_t *sel_ids, const int32_t *n_sel,
                          const int32_t *offsets, const int32_t *pair_tok,
                          const FfnHdr *hdr, const FfnUnit *units, int n_cu,
-                         const uint32_t *tokoff, void *H, hipStream_t st);
+                         const uint32_t *tokoff, const SpRec *rec, const int32_t *sptok, void *H,
+                         hipStream_t st);
 hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K,
                        int budget, int slots, int ns, const void *w2, const void *w2s,
                        const int32_t *sel_ids,
                        const int32_t *n_sel, const int32_t *offsets,
-                       const FfnHdr *hdr, const FfnUnit *units, int n_cu,
+                       const FfnHdr *hdr, const FfnUnit *units, const SpRec *rec, int n_cu,
                        const float *pair_gate, const void *H, float *pairbuf, hipStream_t st);
 // kc: columns of pair_of (K routed + the shared experts)
 hipError_t launch_combine(bool bf16, int B, int d, int kc,

@@ -238,12 +238,13 @@ constexpr int SB_WAVES = SEL_THREADS / WAVE;   // wavefronts of k_select_backfil
 // until the workgroups, one per CU by their LDS, run in one round (E = 128, K =
 // 8, B = 1024: 30.6 us with two tokens in two rounds, 16.2 with four; below
 // the line no difference: B = 400 10.8 and 11.0).
-inline int sb_tokens(int B, int n_cu) {
-  int t = 2;
-  while (t < TOK_GROUP && (B + t - 1) / t > n_cu) t *= 2;
+inline int sb_tokens_log2(int B, int n_cu) {
+  int t = 1;
+  while ((1 << t) < TOK_GROUP && (B + (1 << t) - 1) >> t > n_cu) ++t;
   return t;
 }
-static_assert(TOK_GROUP <= SB_WAVES && TOK_GROUP % 2 == 0, "a token group in whole workgroups");
+constexpr int TOK_GROUP_LOG2 = 4;
+static_assert(TOK_GROUP == 1 << TOK_GROUP_LOG2 && TOK_GROUP <= SB_WAVES, "a token group in whole workgroups");
 
 // Per-wavefront LDS of the backfill
 template <int W>
@@ -393,7 +394,7 @@ void k_backfill(int B, int E, int K, int norm_topk, int flags,
 // execution order -- the values and the order of backfill_body.
 template <int NCH>
 __global__ __launch_bounds__(SEL_THREADS)
-void k_select_backfill(int B, int K, int E, int sbt, const int32_t *__restrict__ ids,
+void k_select_backfill(int B, int K, int E, int sbl, const int32_t *__restrict__ ids,
                        const float *__restrict__ cost, int budget, int binary, int flags,
                        const uint8_t *__restrict__ order, const float *__restrict__ ex,
                        const float *__restrict__ den, float *__restrict__ scores,
@@ -403,13 +404,15 @@ void k_select_backfill(int B, int K, int E, int sbt, const int32_t *__restrict__
   __shared__ SelLds S;
   __shared__ int slot_s[MAX_E];
   const int lane = lane_id(), wv = wave_id();
-  int tg, tq;
-  xcd_group(blockIdx.x, TOK_GROUP / sbt, tg, tq);
+  // xcd_group with TOK_GROUP >> sbl workgroups per group (sbl: log2 of the
+  // tokens per workgroup)
+  const int qb = blockIdx.x / N_XCD, per = TOK_GROUP_LOG2 - sbl;
+  const int tg = blockIdx.x % N_XCD + N_XCD * (qb >> per), tq = qb & ((1 << per) - 1);
   if (tg * TOK_GROUP >= B) return;
-  const bool active = wv < sbt;
+  const bool active = wv < (1 << sbl);
   // the tokens of group tg sit on die tg % N_XCD, where k_tail wrote their
   // rank rows
-  const int t = tg * TOK_GROUP + tq * sbt + wv, tc = min(t, B - 1);
+  const int t = tg * TOK_GROUP + (tq << sbl) + wv, tc = min(t, B - 1);
   int ov[NCH];
   float xv[NCH];
 #pragma unroll
@@ -635,7 +638,8 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
                float *__restrict__ pair_gate, int32_t *__restrict__ pair_of,
                const int32_t *__restrict__ sel_ids, int tables, int d, int I,
                uint32_t *__restrict__ tokoff, FfnHdr *__restrict__ hdr,
-               FfnUnit *__restrict__ units_gu, FfnUnit *__restrict__ units_dn, int n_cu) {
+               FfnUnit *__restrict__ units_gu, FfnUnit *__restrict__ units_dn,
+               SpRec *__restrict__ rec, int32_t *__restrict__ sptok, int n_cu) {
   // cw[w][s]: pairs of slot s in wavefront w, then their first rank in slot s
   __shared__ int cw[CP_WAVES][MAX_E];
   __shared__ int cnt[SCAN_N];
@@ -931,6 +935,23 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
     if (tid < B)
       for (int i = 0; i < ns; ++i) put_tok(n_sel + i, tid, tid);
   }
+  if (rec) {
+    // the split kernels' records and token list, this die's copy
+    SpRec *rx = rec + (size_t)blockIdx.x * (budget + ns);
+    int32_t *tx = sptok + (size_t)blockIdx.x * B * kc;
+    for (int s = tid; s < budget + ns; s += CP_THREADS) {
+      const int q = s < budget ? s : n_sel + (s - budget);
+      const bool kept = s >= budget || s < n_sel;
+      const int u = s < budget ? (kept ? sel_s[s] : 0) : E + (s - budget);
+      // an expert out of range: only for a plan not made by base_select
+      const bool run = kept && u >= 0 && u < E + ns;
+      rx[s] = SpRec{run ? u : 0, run ? off[q] : 0, run ? cnt[q] : 0, 0};
+    }
+    if (tid < B)
+      for (int i = 0; i < ns; ++i) tx[off[n_sel + i] + tid] = tid;
+    __syncthreads();   // stage_t complete
+    for (int i = tid; i < routed; i += CP_THREADS) tx[i] = stage_t[i];
+  }
   if (!out) return;
   __syncthreads();
   for (int i = tid; i < routed; i += CP_THREADS) pair_tok[i] = stage_t[i];
@@ -958,6 +979,305 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
   }
 }
 
+// Selection, backfill and compaction of a small batch (B <= FFN_SPLIT_B: one
+// 64-token chunk, at most PL_THREADS routed pairs) in one launch, for the
+// fused layer, whose routes are distinct.  One workgroup per die (one in all
+// without rec) makes the whole plan -- the arithmetic and the order of
+// select_body and k_select_backfill, so the same results -- and writes its
+// die's slot records; workgroup 0 writes the plan.
+//  * A thread brings one routed pair; its cost goes to V[u][t].  PL_T (32 or
+//    64) token positions: the tree of a chunk whose upper positions are +0 is
+//    that of the lower ones (a cost is never -0).  Four lanes per expert: lane
+//    p holds the positions p, p + 4, .., so that the tree's levels down to 4
+//    are its own and 2, 1 lane exchanges.
+//  * The kept experts' ranks as in select_body.
+//  * A wavefront backfills the tokens wv, wv + 16, ..; executing slot s sets
+//    bit t of mask[s], so that a pair's place is the slot's offset plus the
+//    bits below its own: the sort by (slot, token) without counting passes.
+// The launch is a chain of barriers and LDS round trips on one CU per die; as
+// two launches it paid one more boundary and the reload of what it had just
+// written (Qwen3-shaped B = 16: k_select_backfill 7.6 and k_compact 4.1 us,
+// now 5.4; with the records on the die, gate/up 12.8 -> 11.9 and down 8.1 ->
+// 7.4; B = 64: 7.8 and 7.8, now 8.0).
+constexpr int PL_THREADS = 1024;
+static_assert(FFN_SPLIT_B == WAVE && FFN_SPLIT_B * MAX_K <= PL_THREADS,
+              "one pair per thread, a 64-bit token mask");
+static_assert(4 * MAX_E <= PL_THREADS, "four lanes per expert");
+template <int NCH, int PL_T>
+__global__ __launch_bounds__(PL_THREADS)
+void k_plan_split(int B, int K, int E, int budget, int ns, int binary, int flags,
+                  const int32_t *__restrict__ ids, const float *__restrict__ cost,
+                  const uint8_t *__restrict__ order, const float *__restrict__ ex,
+                  const float *__restrict__ den, const float *__restrict__ gdot,
+                  float *__restrict__ scores, int32_t *__restrict__ counts,
+                  int32_t *__restrict__ sel_ids, int32_t *__restrict__ n_sel_out,
+                  int32_t *__restrict__ slot_of, int32_t *__restrict__ exec_ids,
+                  float *__restrict__ exec_gates, int32_t *__restrict__ offsets,
+                  int32_t *__restrict__ pair_tok, float *__restrict__ pair_gate,
+                  int32_t *__restrict__ pair_of, SpRec *__restrict__ rec,
+                  int32_t *__restrict__ sptok) {
+  constexpr int PL_PAD = PL_T + 1;
+  constexpr int TPW = PL_T / (PL_THREADS / WAVE);   // tokens per wavefront
+  __shared__ float V[MAX_E * PL_PAD];
+  __shared__ int cnt[MAX_E];
+  __shared__ __attribute__((aligned(16))) uint64_t key[MAX_E];
+  __shared__ int slot_s[MAX_E], sel_s[MAX_E];
+  __shared__ uint64_t mask[MAX_E];
+  __shared__ int off[MAX_E + 1];
+  __shared__ int n_union;
+  const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+  const bool out = blockIdx.x == 0;
+  const int kc = K + ns, nq = B * K;
+  // every global load first
+  const int ic = min(tid, nq - 1);
+  const int u_r = ids[ic];
+  const float c_r = cost[ic];
+  int ov[TPW][NCH];
+  float xv[TPW][NCH], dv[TPW];
+#pragma unroll
+  for (int q = 0; q < TPW; ++q) {
+    const int tc = min(wv + q * (PL_THREADS / WAVE), B - 1);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int r = min(WAVE * c + lane, E - 1);
+      ov[q][c] = order[(size_t)tc * E + r];
+      xv[q][c] = ex[(size_t)tc * E + r];
+    }
+    dv[q] = den[tc];
+  }
+  const float gd = gdot ? gdot[min(tid, B - 1)] : 0.0f;
+  const int t_r = tid / K;
+  for (int i = tid; i < E * PL_PAD; i += PL_THREADS) V[i] = 0.0f;
+  if (tid < E) {
+    cnt[tid] = 0;
+    mask[tid] = 0ull;
+  }
+  if (tid == 0) n_union = 0;
+  __syncthreads();
+  if (tid < nq && u_r >= 0 && u_r < E) {
+    V[u_r * PL_PAD + t_r] = c_r;
+    atomicAdd(&cnt[u_r], 1);
+  }
+  __syncthreads();
+  {
+    const int u = tid >> 2, p = tid & 3;
+    const bool have = u < E;
+    float v[PL_T / 4];
+#pragma unroll
+    for (int i = 0; i < PL_T / 4; ++i) v[i] = have ? V[u * PL_PAD + p + 4 * i] : 0.0f;
+#pragma unroll
+    for (int h = PL_T / 8; h >= 1; h >>= 1)
+#pragma unroll
+      for (int i = 0; i < h; ++i) v[i] = v[i] + v[i + h];
+    float D = v[0];
+    D = D + xor_lane<2>(D);
+    D = D + xor_lane<1>(D);
+    const int n = have ? cnt[u] : 0;
+    const bool in = n > 0;
+    if (have && p == 0) {
+      const float kv = binary ? (D > 0.0f ? 1.0f : 0.0f) : D;
+      key[u] = in ? rank_key(kv, u) : 0;
+      if (out) {
+        scores[u] = D;
+        counts[u] = n;
+      }
+    } else if (!have && p == 0 && u < MAX_E) {
+      key[u] = 0;   // ranks after every expert
+    }
+    const uint64_t m = __ballot(in && p == 0);
+    if (lane == 0 && m) atomicAdd(&n_union, (int)__popcll(m));
+  }
+  __syncthreads();
+  const int n_sel = min(budget, n_union);
+  {
+    // tpe consecutive threads per expert over interleaved key pairs, as in
+    // select_body
+    int E2 = WAVE;
+    while (E2 < E) E2 <<= 1;
+    const int tpe = PL_THREADS / E2, npair = E2 / (2 * tpe);
+    const int u = tid / tpe, part = tid % tpe;
+    const uint64_t ku = key[u];
+    int r = 0;
+    for (int i0 = 0; i0 < npair; i0 += 8) {
+      u32x4 o[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (i0 + q < npair)
+          o[q] = *reinterpret_cast<const u32x4 *>(&key[2 * (part + tpe * (i0 + q))]);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (i0 + q < npair) {
+          r += (((uint64_t)o[q].y << 32 | o[q].x) > ku);
+          r += (((uint64_t)o[q].w << 32 | o[q].z) > ku);
+        }
+    }
+    for (int h = 1; h < tpe; h <<= 1) r += __shfl_xor(r, h, WAVE);
+    if (u < E && part == 0) {
+      const int slot = ku != 0 && r < n_sel ? r : -1;
+      slot_s[u] = slot;
+      if (slot >= 0) sel_s[slot] = u;
+      if (out) {
+        slot_of[u] = slot;
+        if (slot >= 0) sel_ids[slot] = u;
+      }
+    }
+    if (out) {
+      for (int r2 = n_sel + tid; r2 < budget; r2 += PL_THREADS) sel_ids[r2] = -1;
+      if (tid == 0) *n_sel_out = n_sel;
+    }
+  }
+  __syncthreads();
+  // backfill (k_select_backfill's): position tj, slot ts and gate gt of the
+  // expert this lane holds in chunk c, if executed
+  const int kp = min(K, n_sel);
+  const bool drop = flags & 2, renorm = flags & 1;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int tj[TPW][NCH], ts[TPW][NCH];
+  float gt[TPW][NCH];
+#pragma unroll
+  for (int q = 0; q < TPW; ++q) {
+    const int t = wv + q * (PL_THREADS / WAVE);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) tj[q][c] = -1;
+    if (t >= B) continue;
+    int nx = 0;
+    float Ssum = 0.0f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      if (drop ? c == 0 : nx < kp) {
+        const int e = ov[q][c];
+        const int sl = e < E ? slot_s[e] : -1;
+        const bool cand = (drop ? lane < K : WAVE * c + lane < E) && sl >= 0;
+        const int j = nx + __popcll(__ballot(cand) & below);
+        const bool take = cand && (drop || j < kp);
+        if (take) {
+          tj[q][c] = j;
+          ts[q][c] = sl;
+          atomicOr((unsigned long long *)&mask[sl], 1ull << t);
+        }
+        uint64_t mt = __ballot(take);
+        nx += __popcll(mt);
+        if (renorm) {
+          while (mt) {
+            const int b = __builtin_ctzll(mt);
+            Ssum = Ssum + __builtin_bit_cast(
+                              float, __builtin_amdgcn_readlane(__float_as_int(xv[q][c]), b));
+            mt &= mt - 1;
+          }
+        }
+      }
+    }
+    if (!renorm) Ssum = dv[q];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      if (tj[q][c] >= 0) {
+        gt[q][c] = xv[q][c] / Ssum;
+        if (out) {
+          exec_ids[(size_t)t * K + tj[q][c]] = ov[q][c];
+          exec_gates[(size_t)t * K + tj[q][c]] = gt[q][c];
+        }
+      }
+    if (out && lane < K && lane >= nx) {
+      exec_ids[(size_t)t * K + lane] = -1;
+      exec_gates[(size_t)t * K + lane] = 0.0f;
+      pair_of[(size_t)t * kc + lane] = -1;
+    }
+  }
+  __syncthreads();
+  if (wv == 0) {   // exclusive prefixes of the slots' pair counts
+    constexpr int Q = MAX_E / WAVE;
+    int l[Q], s0 = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const int s = Q * lane + i;
+      l[i] = s < n_sel ? __popcll(mask[s]) : 0;
+      s0 += l[i];
+    }
+    int inc = s0;
+#pragma unroll
+    for (int h = 1; h < WAVE; h <<= 1) {
+      const int o = __shfl_up(inc, h, WAVE);
+      if (lane >= h) inc += o;
+    }
+    int r = inc - s0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      off[Q * lane + i] = r;
+      r += l[i];
+    }
+    if (lane == WAVE - 1) off[MAX_E] = r;
+  }
+  __syncthreads();
+  const int routed = off[MAX_E];   // off[s] = routed for s >= n_sel
+  int32_t *tx = rec ? sptok + (size_t)blockIdx.x * B * kc : nullptr;
+#pragma unroll
+  for (int q = 0; q < TPW; ++q)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      if (tj[q][c] >= 0) {
+        const int t = wv + q * (PL_THREADS / WAVE), s = ts[q][c];
+        const int p = off[s] + __popcll(mask[s] & ((1ull << t) - 1ull));
+        if (rec) tx[p] = t;
+        if (out) {
+          pair_tok[p] = t;
+          pair_gate[p] = gt[q][c];
+          pair_of[(size_t)t * kc + tj[q][c]] = p;
+        }
+      }
+  if (rec) {
+    SpRec *rx = rec + (size_t)blockIdx.x * (budget + ns);
+    for (int s = tid; s < budget + ns; s += PL_THREADS) {
+      const int i = s - budget;
+      rx[s] = i >= 0 ? SpRec{E + i, routed + i * B, B, 0}
+                     : (s < n_sel ? SpRec{sel_s[s], off[s], (int)__popcll(mask[s]), 0} : SpRec{0, 0, 0, 0});
+    }
+    if (tid < B)
+      for (int i = 0; i < ns; ++i) tx[routed + i * B + tid] = tid;
+  }
+  if (!out) return;
+  for (int s = tid; s <= budget + ns; s += PL_THREADS)
+    offsets[s] = s <= budget ? off[min(s, MAX_E)] : routed + (s - budget) * B;
+  if (tid < B) {
+    float gs = 1.0f;
+    if (gdot) {
+      const float e = base_exp(-gd);
+      const float dn = 1.0f + e;
+      gs = 1.0f / dn;
+    }
+    for (int i = 0; i < ns; ++i) {
+      const int p = routed + i * B + tid;
+      pair_tok[p] = tid;
+      pair_gate[p] = gs;
+      pair_of[(size_t)tid * kc + K + i] = p;
+    }
+  }
+}
+
+hipError_t launch_plan_split(int B, int K, int E, int budget, int ns, bool binary, int flags,
+                             const int32_t *ids, const float *cost, const uint8_t *order,
+                             const float *ex, const float *den, const float *gdot,
+                             float *scores, int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
+                             int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
+                             int32_t *offsets, int32_t *pair_tok, float *pair_gate,
+                             int32_t *pair_of, SpRec *rec, int32_t *sptok, hipStream_t st) {
+#define BASE_PL(C, T)                                                                            \
+  launch_k(k_plan_split<C, T>, dim3(rec ? N_XCD : 1), dim3(PL_THREADS), 0, st, B, K, E, budget,  \
+           ns, (int)binary, flags, ids, cost, order, ex, den, gdot, scores, counts, sel_ids,     \
+           n_sel, slot_of, exec_ids, exec_gates, offsets, pair_tok, pair_gate, pair_of, rec,     \
+           sptok)
+  if (B <= 32) {
+    if (E <= WAVE) BASE_PL(1, 32);
+    else if (E <= 2 * WAVE) BASE_PL(2, 32);
+    else BASE_PL(4, 32);
+  } else {
+    if (E <= WAVE) BASE_PL(1, 64);
+    else if (E <= 2 * WAVE) BASE_PL(2, 64);
+    else BASE_PL(4, 64);
+  }
+#undef BASE_PL
+  return hipGetLastError();
+}
+
 hipError_t launch_select(int B, int K, int E, const int32_t *ids,
                          const float *cost, int budget, bool binary, float *scores,
                          int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
@@ -973,10 +1293,10 @@ hipError_t launch_select_backfill(int B, int K, int E, const int32_t *ids, const
                                   int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
                                   int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
                                   int n_cu, hipStream_t st) {
-  const int sbt = sb_tokens(B, n_cu);
-  const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP / sbt));
+  const int sbl = sb_tokens_log2(B, n_cu);
+  const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP >> sbl));
 #define BASE_SB(C)                                                                         \
-  launch_k(k_select_backfill<C>, grid, dim3(SEL_THREADS), 0, st, B, K, E, sbt, ids, cost, budget, \
+  launch_k(k_select_backfill<C>, grid, dim3(SEL_THREADS), 0, st, B, K, E, sbl, ids, cost, budget, \
            (int)binary, flags, order, ex, den, scores, counts, sel_ids, n_sel, slot_of,     \
            exec_ids, exec_gates)
   if (E <= WAVE) BASE_SB(1);
@@ -1003,14 +1323,15 @@ hipError_t launch_compact(int B, int K, int E, int budget, int ns, const int32_t
                           int32_t *pair_tok, float *pair_gate,
                           int32_t *pair_of, const int32_t *sel_ids, bool tables, int d,
                           int I, uint32_t *tokoff, FfnHdr *hdr, FfnUnit *units_gu,
-                          FfnUnit *units_dn, int n_cu, hipStream_t st) {
+                          FfnUnit *units_dn, SpRec *rec, int32_t *sptok, int n_cu,
+                          hipStream_t st) {
   const int ppt = (B * K + CP_THREADS - 1) / CP_THREADS;
   const uint64_t kmul = ((1ull << 32) + (uint64_t)K - 1) / (uint64_t)K;
-  const unsigned blocks = tables ? N_XCD : 1u;   // one workgroup per die
+  const unsigned blocks = tables || rec ? N_XCD : 1u;   // one workgroup per die
 #define BASE_COMPACT(P)                                                                    \
   launch_k(k_compact<P>, dim3(blocks), dim3(CP_THREADS), 0, st, B, K, kmul, E, budget, ns, \
            exec_ids, exec_gates, slot_of, n_sel, gdot, offsets, pair_tok, pair_gate,      \
-           pair_of, sel_ids, (int)tables, d, I, tokoff, hdr, units_gu, units_dn, n_cu)
+           pair_of, sel_ids, (int)tables, d, I, tokoff, hdr, units_gu, units_dn, rec, sptok, n_cu)
   if (ppt <= 1) BASE_COMPACT(1);
   else if (ppt <= 2) BASE_COMPACT(2);
   else if (ppt <= 4) BASE_COMPACT(4);

@@ -1,4 +1,4 @@
-"""The FFN's split kernels (batches of at most 32 tokens): tile edges of the
+"""The FFN's split kernels (batches of at most 64 tokens): tile edges of the
 tokens, contractions shorter than the wavefronts' shares, slots of several
 passes, kept sets that the caller brings."""
 import numpy as np
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("B", [1, 15, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65])
 @pytest.mark.parametrize("d,E,K,I,ns,budget", [
     (256, 8, 2, 64, 0, 3),       # eight k-steps of d, two of I: most shares of I empty
     (768, 24, 5, 192, 2, 9),     # shares of unequal length, shared experts
@@ -51,7 +51,7 @@ def _forward(gu, inp, logits, ids, sel, n_sel, slot, budget, flags):  # noqa: F8
     return offsets
 
 
-@pytest.mark.parametrize("B", [16, 29])
+@pytest.mark.parametrize("B", [16, 29, 60])
 def test_slot_of_several_passes(gu, B):  # noqa: F811
     """Routes that name one expert up to four times, executed as they are
     (drop): a slot then holds more pairs than one pass's token tiles."""
@@ -63,7 +63,7 @@ def test_slot_of_several_passes(gu, B):  # noqa: F811
     slot = np.full(12, -1, np.int32)
     slot[[3, 7]] = [1, 0]
     offsets = _forward(gu, inp, logits, ids, np.array([7, 3]), 2, slot, 2, 2)
-    assert offsets[2] - offsets[1] > 32
+    assert offsets[2] - offsets[1] > 16 * (1 if B <= 16 else 2 if B <= 32 else 4)
 
 
 def test_kept_set_beyond_the_routes(gu):  # noqa: F811
@@ -83,6 +83,25 @@ def test_fp32_rows(gu, B, d, I):  # noqa: F811
     """fp32 layers: token batches of eight and their remainders, a row of I
     shorter than a wavefront's pass and one with a remainder."""
     run_case(gu, W.custom_layer(d, 6, 3, I, B, bf16=False, seed=80 + B), 4, flags=2)
+
+
+@pytest.mark.parametrize("B", [1, 32, 33, 64])
+@pytest.mark.parametrize("E,K,rule,flags", [(40, 3, 1, 0), (65, 16, 0, 3), (256, 16, 4, 1),
+                                            (130, 9, 2, 2)])
+def test_one_launch_plan(gu, B, E, K, rule, flags):  # noqa: F811
+    """Selection, backfill and compaction in one launch: every plan array
+    against the oracle and the staged calls, over the chunk widths of the
+    experts and the tokens, ties of the binary rule, all the gate and fill
+    flags."""
+    inp = W.custom_layer(256, E, K, 64, B, seed=95 + K, n_shared=K % 2)
+    run_case(gu, inp, max(1, E // 3), flags=flags, score_rule=rule, norm_topk=K % 2)
+    run_case(gu, inp, E, flags=flags, score_rule=rule, norm_topk=K % 2)
+
+
+def test_long_contraction(gu):  # noqa: F811
+    """The split kernels' bound for a long contraction of I."""
+    for B in (32, 33):
+        run_case(gu, W.custom_layer(256, 5, 2, 2112, B, seed=97), 3)
 
 
 @pytest.mark.parametrize("B", [511, 513, 600])
