@@ -152,6 +152,8 @@ Layout layout(const base_layer *L, int32_t B, int32_t bc) {
   // (small batches: gate/up's token lists, one per die, lie here until down
   // writes its rows)
   o.pairbuf = take(P * L->d * 4);
+  static_assert(MAX_E <= 256 && SC_SMALL_B <= 2 * 16 * 64 / 4,
+                "q [B][E] in B rows of d >= 256 floats, ss [B] in one activation tile");
   o.total = at;
   return o;
 }
@@ -439,15 +441,19 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
   int32_t *nsel = at<int32_t>(ws, o.n_sel);
   int32_t *slot = at<int32_t>(ws, o.slot_of);
   stage(0, st);
+  // a small batch's launch also makes the predictor's dot products: q lies in
+  // the pair rows' buffer and ||x||^2 in the activations', free until the FFN
+  const bool dense = scores_small(B) && L->score_rule == BASE_SCORE_BASE;
+  float *qd = dense ? at<float>(ws, o.pairbuf) : nullptr, *ss = dense ? at<float>(ws, o.H) : nullptr;
   HIP_TRY(launch_scores(bf16, x, B, L->d, L->w_router, L->b_router, L->E, shared_gate(L),
-                        logits, at<float>(ws, o.gdot), st));
+                        logits, at<float>(ws, o.gdot), st, dense ? L->pred_a : nullptr, qd, ss));
   stage_end(st);
   uint8_t *order = at<uint8_t>(ws, o.order);
   float *ex = at<float>(ws, o.ex), *den = at<float>(ws, o.den);
   stage(1, st);   // top-K, weights, (the method's rule) the routed pairs' predictor,
               // and each token's experts in rank order for the backfill
   HIP_TRY(launch_tail(bf16, B, L->E, L->K, L->d, L->norm_topk, logits, x, L->pred_a,
-                      L->pred_b, ids, w, cost, 3, L->score_rule, st, order, ex, den));
+                      L->pred_b, ids, w, cost, 3, L->score_rule, st, order, ex, den, qd, ss));
   stage_end(st);
   stage(2, st);   // selection and backfill in one launch
   const bool split = ffn_split(B, L->I);   // ... and, for a small batch, the compaction

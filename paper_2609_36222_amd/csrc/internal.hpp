@@ -169,9 +169,15 @@ __host__ __device__ inline unsigned ffn_dn_grid(int n_cu, int kind) {
 }
 
 // rows: n_router of Wr (logits, + beta), then the vector G when given (gdot)
+// scores_small batches may also take the predictor's rows A [n_router]: the
+// dot products of every expert (q [B][n_router]) and ||x||^2 (ss [B]); where
+// the line lies: k_scores_small
+constexpr int SC_SMALL_B = 64;
+inline bool scores_small(int B) { return B <= SC_SMALL_B; }
 hipError_t launch_scores(bool bf16, const void *x, int B, int d, const float *Wr,
                          const float *beta, int n_router, const float *G, float *logits,
-                         float *gdot, hipStream_t st);
+                         float *gdot, hipStream_t st, const float *A = nullptr,
+                         float *q = nullptr, float *ss = nullptr);
 // Selection rules (the values of BASE_SCORE_* in base.h): the per-pair
 // score k_tail writes as the cost
 constexpr int SCORE_BASE = 0, SCORE_TOP1 = 1, SCORE_WEIGHT = 2, SCORE_WEIGHT_SQ = 3,
@@ -181,11 +187,14 @@ constexpr int SCORE_BASE = 0, SCORE_TOP1 = 1, SCORE_WEIGHT = 2, SCORE_WEIGHT_SQ 
 // order / ex / den (optional, route mode): per token the experts in rank
 // order [B][E] (bytes), exp(l - l_max) in rank order [B][E] and the router's
 // softmax denominator S [B], for the fused layer's backfill
+// q / ss (optional, SCORE_BASE): the predictor's dot products and ||x||^2 from
+// launch_scores; x and A are then not read
 hipError_t launch_tail(bool bf16, int B, int E, int K, int d, int norm_topk,
                        const float *logits, const void *x, const float *A, const float *bp,
                        int32_t *ids, float *w, float *cost, int mode, int rule,
                        hipStream_t st, uint8_t *order = nullptr, float *ex = nullptr,
-                       float *den = nullptr);
+                       float *den = nullptr, const float *q = nullptr,
+                       const float *ss = nullptr);
 // binary: rank by (score > 0) instead of the score (the top-1-union rule)
 hipError_t launch_select(int B, int K, int E, const int32_t *ids,
                          const float *cost, int budget, bool binary, float *scores,

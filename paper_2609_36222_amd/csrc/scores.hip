@@ -215,6 +215,137 @@ void k_scores(const XT *__restrict__ x, int B, int d,
   }
 }
 
+// Small batches (B <= SC_SMALL_B).  The tiled kernel's few workgroups (16 at B
+// <= 16, on one die) walk their chunks behind LDS barriers; here a wavefront
+// takes 4 tokens x 4 rows straight into registers, SS_GC chunks of 256
+// elements at a time with the next ones in flight, and nothing is shared, so
+// the launch is one memory latency, 256 FMAs and a tree.  With the chip
+// otherwise idle it also makes the predictor's dot products with every
+// expert (A, q) and ||x||^2 (ss), which k_tail would otherwise start only once
+// the routing is known.  Each dot product in the fixed order.
+// A workgroup is 4 wavefronts: 16 tokens (a token group) x 4 rows.  The router
+// rows of token group g run on die g % N_XCD, where k_tail reads the logits;
+// the predictor's and the extra rows (G; x itself) on the other dies: workgroup
+// b on die b % N_XCD is number b / N_XCD there.
+// Scores + tail, against the tiled kernel and the predictor in the tail (E =
+// 128, d = 2048, us): B = 1 7.6 + 5.1 -> 4.8 + 4.0, B = 16 7.8 + 5.5 -> 5.7 + 4.0,
+// B = 64 8.0 + 5.6 -> 7.6 + 4.0; E = 8, d = 4096, B = 16 13.3 + 4.8 -> 9.0 +
+// 4.0.  Beyond 64 tokens the unshared reads (48 KB a wavefront) catch up with
+// what the tiles save.  Four chunks at a time: equal, slower at d = 256.
+constexpr int SS_GC = 2;
+static_assert(SC_SMALL_B / TOK_GROUP < N_XCD, "a die left for the predictor's rows");
+
+template <typename XT>
+__global__ __launch_bounds__(4 * WAVE, 2)
+void k_scores_small(const XT *__restrict__ x, int B, int d, const float *__restrict__ Wr,
+                    const float *__restrict__ beta, int E, const float *__restrict__ A,
+                    const float *__restrict__ G, int n_group, int n_other,
+                    float *__restrict__ logits, float *__restrict__ q, float *__restrict__ ss,
+                    float *__restrict__ gdot) {
+  const int lane = lane_id(), w = wave_id_u();
+  const int die = blockIdx.x % N_XCD, nb = blockIdx.x / N_XCD;
+  const int rgs = (E + 3) / 4;   // row groups of 4
+  int g, rg;
+  const bool router = die < n_group;
+  if (router) {
+    g = die;
+    rg = nb;
+    if (rg >= rgs) return;
+  } else {
+    // the rest, token group by token group: pgs predictor groups, one of extras
+    const int i = nb * (N_XCD - n_group) + die - n_group;
+    if (i >= n_other) return;
+    const int per = n_other / n_group;
+    g = i / per;
+    rg = i - g * per;
+  }
+  const int t0 = g * TOK_GROUP + 4 * w;
+  if (t0 >= B) return;
+  const bool extra = !router && (A == nullptr || rg >= rgs);
+  const XT *xr[4];
+  const float *wr[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) xr[a] = x + (size_t)min(t0 + a, B - 1) * d + 4 * lane;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+    wr[b] = extra ? (G ? G + 4 * lane : nullptr)
+                  : (router ? Wr : A) + (size_t)min(4 * rg + b, E - 1) * d + 4 * lane;
+  float acc[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+  if (extra) {   // rows: 0 x itself, 1 G
+    for (int m = 0; m < d; m += 256) {
+      float gv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (G) load4(wr[0] + m, gv);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        float xv[4];
+        load4(xr[a] + m, xv);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          acc[4 * a] = __builtin_fmaf(xv[r], xv[r], acc[4 * a]);
+          acc[4 * a + 1] = __builtin_fmaf(xv[r], gv[r], acc[4 * a + 1]);
+        }
+      }
+    }
+  } else {
+    Raw4<XT> xv[2][SS_GC][4];
+    float4 wv[2][SS_GC][4];
+    auto fetch = [&](int s, int m0) {
+#pragma unroll
+      for (int c = 0; c < SS_GC; ++c) {
+        const int m = min(m0 + 256 * c, d - 256);   // past the end: not used
+#pragma unroll
+        for (int b = 0; b < 4; ++b) wv[s][c][b] = *reinterpret_cast<const float4 *>(wr[b] + m);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) xv[s][c][a].load(xr[a] + m);
+      }
+    };
+    auto use = [&](int s, int m0) {
+#pragma unroll
+      for (int c = 0; c < SS_GC; ++c) {
+        if (m0 + 256 * c >= d) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            const float xe = xv[s][c][a].at(r);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+              const float we = r == 0   ? wv[s][c][b].x
+                               : r == 1 ? wv[s][c][b].y
+                               : r == 2 ? wv[s][c][b].z
+                                        : wv[s][c][b].w;
+              acc[4 * a + b] = __builtin_fmaf(xe, we, acc[4 * a + b]);
+            }
+          }
+      }
+    };
+    fetch(0, 0);
+    for (int m0 = 0; m0 < d; m0 += 2 * SS_GC * 256) {
+      fetch(1, m0 + SS_GC * 256);
+      __builtin_amdgcn_sched_barrier(0);
+      use(0, m0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (m0 + 2 * SS_GC * 256 < d) fetch(0, m0 + 2 * SS_GC * 256);
+      __builtin_amdgcn_sched_barrier(0);
+      if (m0 + SS_GC * 256 < d) use(1, m0 + SS_GC * 256);
+    }
+  }
+  const float v = tree16(acc);   // dot i of (token i / 4, row i % 4) in lanes 4 i ..
+  const int i = lane >> 2, t = t0 + (i >> 2), b = i & 3, r = 4 * rg + b;
+  if ((lane & 3) != 0 || t >= B) return;
+  if (extra) {
+    if (b == 0 && ss) ss[t] = v;
+    if (b == 1 && G) gdot[t] = v;
+  } else if (r < E) {
+    if (router)
+      logits[(size_t)t * E + r] = beta ? v + beta[r] : v;
+    else
+      q[(size_t)t * E + r] = v;
+  }
+}
+
 constexpr int TL_NI = MAX_E / WAVE;
 constexpr int TL_RANK = 256;                  // lanes that rank the logits
 constexpr int TL_MAXW = (MAX_K + 1) / 2 > TL_RANK / WAVE ? (MAX_K + 1) / 2 : TL_RANK / WAVE;
@@ -224,6 +355,19 @@ constexpr int TL_MAXW = (MAX_K + 1) / 2 > TL_RANK / WAVE ? (MAX_K + 1) / 2 : TL_
 __host__ __device__ inline int tail_waves(int K, bool pred) {
   const int wp = pred ? (K + 1) / 2 : 0;
   return wp > TL_RANK / WAVE ? wp : TL_RANK / WAVE;
+}
+
+// w^2 exp(q / ||x|| + b), ss = ||x||^2, in the fixed order.
+__device__ __forceinline__ float pair_cost(float q, float ss, float b, float w) {
+  float inv = 0.0f;
+  if (ss > 0.0f) {
+    const float rt = sqrtf(ss);
+    inv = 1.0f / rt;
+  }
+  float s = q * inv;
+  s = s + b;
+  const float w2 = w * w;
+  return w2 * base_exp(s);
 }
 
 // mode bit 0: route (top-K and weights from the logits into ids / w)
@@ -247,17 +391,20 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
             const XT *__restrict__ x, const float *__restrict__ A,
             const float *__restrict__ bp, int32_t *__restrict__ ids_io,
             float *__restrict__ w_io, float *__restrict__ cost, int mode, int rule,
-            uint8_t *__restrict__ order, float *__restrict__ ex, float *__restrict__ den) {
+            uint8_t *__restrict__ order, float *__restrict__ ex, float *__restrict__ den,
+            const float *__restrict__ qd, const float *__restrict__ ssd) {
   __shared__ __attribute__((aligned(16))) uint64_t keys[MAX_E];
   __shared__ float lrow[MAX_E];
   __shared__ int part[TL_RANK];
   __shared__ int route[MAX_K];
+  __shared__ float qrow[MAX_E];
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id_u();
   int tg, ti;
   xcd_group(blockIdx.x, TOK_GROUP, tg, ti);
   const int t = tg * TOK_GROUP + ti;   // on the die that wrote its logits
   if (t >= B) return;
-  const bool pred = (mode & 2) && rule == SCORE_BASE;
+  // the predictor's dot products: made here, or (qd, ssd) by k_scores_small
+  const bool pred = (mode & 2) && rule == SCORE_BASE && !qd;
   // the logits row (clamped, no branches, so that the loads are in flight
   // together); the method's predictor's first pass of the token row is
   // requested once the routing's inputs have arrived (it does not depend on
@@ -266,6 +413,12 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
   if ((mode & 1) && w == 0) {
 #pragma unroll
     for (int i = 0; i < TL_NI; ++i) lv[i] = logits[(size_t)t * E + min(lane + WAVE * i, E - 1)];
+  }
+  float qv[TL_NI], ssv = 0.0f;
+  if (qd && w == 0) {   // written on other dies: they arrive while the routing runs
+#pragma unroll
+    for (int i = 0; i < TL_NI; ++i) qv[i] = qd[(size_t)t * E + min(lane + WAVE * i, E - 1)];
+    ssv = ssd[t];
   }
   constexpr int GC = 8;   // chunks of 256 elements per pass, loads issued together
   const XT *xr = x + (size_t)t * d + 4 * lane;
@@ -360,6 +513,14 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
   if (!(mode & 2)) return;
 
   const int u = (lane < K && my_id >= 0 && my_id < E) ? my_id : 0;   // out-of-range ids read row 0
+  if (qd) {   // the method's rule on k_scores_small's dot products
+    if (w != 0) return;
+#pragma unroll
+    for (int i = 0; i < TL_NI; ++i)
+      if (lane + WAVE * i < E) qrow[lane + WAVE * i] = qv[i];
+    if (lane < K) cost[(size_t)t * K + lane] = pair_cost(qrow[u], ssv, bp[u], my_w);
+    return;
+  }
   if (!pred) {
     if (w == 0 && lane < K) {
       float c;
@@ -414,23 +575,22 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
   ss = wave_tree_sum(ss);
   q0 = wave_tree_sum(q0);
   if (has1) q1 = wave_tree_sum(q1);
-  float inv = 0.0f;
-  if (ss > 0.0f) {
-    const float rt = sqrtf(ss);
-    inv = 1.0f / rt;
-  }
-  if (lane == k0 || (has1 && lane == k1)) {
-    float s = (lane == k0 ? q0 : q1) * inv;
-    s = s + b_my;
-    const float w2 = my_w * my_w;
-    cost[(size_t)t * K + lane] = w2 * base_exp(s);
-  }
+  if (lane == k0 || (has1 && lane == k1))
+    cost[(size_t)t * K + lane] = pair_cost(lane == k0 ? q0 : q1, ss, b_my, my_w);
 }
 
 template <typename XT>
 static void launch_scores_t(const XT *x, int B, int d, const float *Wr, const float *beta,
                             int n_router, const float *G, float *logits, float *gdot,
-                            hipStream_t st) {
+                            const float *A, float *q, float *ss, hipStream_t st) {
+  if (scores_small(B)) {
+    const int n_group = (B + TOK_GROUP - 1) / TOK_GROUP, rgs = (n_router + 3) / 4;
+    const int n_other = n_group * ((A ? rgs : 0) + (A || G ? 1 : 0));
+    const int dies = N_XCD - n_group, nb = (n_other + dies - 1) / dies;
+    launch_k(k_scores_small<XT>, dim3(N_XCD * (rgs > nb ? rgs : nb)), dim3(4 * WAVE), 0, st, x, B,
+             d, Wr, beta, n_router, A, G, n_group, n_other, logits, q, ss, gdot);
+    return;
+  }
   const int rows = n_router + (G ? 1 : 0);
   const dim3 grid(xcd_grid((B + SC_TB - 1) / SC_TB, (rows + SC_RB - 1) / SC_RB));
   launch_k(k_scores<XT>, grid, dim3(SC_WAVES * WAVE), 0, st, x, B, d, Wr, beta, n_router, G,
@@ -439,26 +599,27 @@ static void launch_scores_t(const XT *x, int B, int d, const float *Wr, const fl
 
 hipError_t launch_scores(bool bf16, const void *x, int B, int d, const float *Wr,
                          const float *beta, int n_router, const float *G, float *logits,
-                         float *gdot, hipStream_t st) {
+                         float *gdot, hipStream_t st, const float *A, float *q, float *ss) {
   if (bf16)
-    launch_scores_t((const uint16_t *)x, B, d, Wr, beta, n_router, G, logits, gdot, st);
+    launch_scores_t((const uint16_t *)x, B, d, Wr, beta, n_router, G, logits, gdot, A, q, ss, st);
   else
-    launch_scores_t((const float *)x, B, d, Wr, beta, n_router, G, logits, gdot, st);
+    launch_scores_t((const float *)x, B, d, Wr, beta, n_router, G, logits, gdot, A, q, ss, st);
   return hipGetLastError();
 }
 
 hipError_t launch_tail(bool bf16, int B, int E, int K, int d, int norm_topk,
                        const float *logits, const void *x, const float *A, const float *bp,
                        int32_t *ids, float *w, float *cost, int mode, int rule,
-                       hipStream_t st, uint8_t *order, float *ex, float *den) {
-  const dim3 block(tail_waves(K, (mode & 2) && rule == SCORE_BASE) * WAVE);
+                       hipStream_t st, uint8_t *order, float *ex, float *den, const float *q,
+                       const float *ss) {
+  const dim3 block(tail_waves(K, (mode & 2) && rule == SCORE_BASE && !q) * WAVE);
   const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP));
   if (bf16)
     launch_k(k_tail<uint16_t>, grid, block, 0, st, B, E, K, d, norm_topk, logits,
-             (const uint16_t *)x, A, bp, ids, w, cost, mode, rule, order, ex, den);
+             (const uint16_t *)x, A, bp, ids, w, cost, mode, rule, order, ex, den, q, ss);
   else
     launch_k(k_tail<float>, grid, block, 0, st, B, E, K, d, norm_topk, logits,
-             (const float *)x, A, bp, ids, w, cost, mode, rule, order, ex, den);
+             (const float *)x, A, bp, ids, w, cost, mode, rule, order, ex, den, q, ss);
   return hipGetLastError();
 }
 

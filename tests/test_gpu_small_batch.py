@@ -85,6 +85,17 @@ def test_fp32_rows(gu, B, d, I):  # noqa: F811
     run_case(gu, W.custom_layer(d, 6, 3, I, B, bf16=False, seed=80 + B), 4, flags=2)
 
 
+@pytest.mark.parametrize("B", [1, 4, 5, 16, 17, 63, 64, 65])
+@pytest.mark.parametrize("d,E,bf16,sg", [(256, 3, True, 1), (768, 37, False, 0), (1024, 256, True, 0),
+                                         (2304, 8, True, 1)])
+def test_small_scores(gu, B, d, E, bf16, sg):  # noqa: F811
+    """Router, predictor and extra rows in one launch: token and row
+    remainders, chunks of the contraction that do not fill a pass."""
+    inp = W.custom_layer(d, E, min(E, 5), 64, B, bf16=bf16, seed=98, n_shared=sg,
+                         shared_gate=bool(sg), zero_token=True)
+    run_case(gu, inp, max(1, E // 2))
+
+
 @pytest.mark.parametrize("B", [1, 32, 33, 64])
 @pytest.mark.parametrize("E,K,rule,flags", [(40, 3, 1, 0), (65, 16, 0, 3), (256, 16, 4, 1),
                                             (130, 9, 2, 2)])
