@@ -801,7 +801,13 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
       if (cost < best_cost) { rp = c; best_cost = cost; }
     }
     // down's row group: FFN_WAVES row tiles, or for a long contraction (one
-    // workgroup per CU) fewer when that gives the busiest workgroup fewer
+    // workgroup per CU) fewer when that gives the busiest workgroup less to
+    // read.  A k-step of a unit reads its rows' weights (1 KiB a row tile) and
+    // its part's tokens (1 KiB a tile), so a smaller row group reads the tokens
+    // more often: the cost is rounds x (row tiles + the mean part's tiles).
+    // Mixtral-shaped, four experts, down in us: B = 128 (4.5 tiles a part) 126
+    // with 8 row tiles, 98 with 4; B = 256 (8 tiles) 157 with 8, 320 with 2,
+    // which the weights alone would choose.
     const int Td = d / 16;
     int rd = FFN_WAVES;
     if (ffn_dn_long(I)) {
@@ -819,7 +825,7 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
       for (int c = FFN_WAVES; c >= 2; c /= 2) {
         const int units = whole ? pdmax * ((Td + c - 1) / c)
                                 : (Pd * ((Td + c - 1) / c) + N_XCD - 1) / N_XCD;
-        const int cost = (int)ceilf((float)units / wgs) * c;
+        const int cost = (int)ceilf((float)units / wgs) * (c * Pd + tb[SCAN_N]);
         if (cost < best) { rd = c; best = cost; }
       }
     }

@@ -110,9 +110,11 @@ def test_one_launch_plan(gu, B, E, K, rule, flags):  # noqa: F811
 
 
 def test_long_contraction(gu):  # noqa: F811
-    """The split kernels' bound for a long contraction of I."""
-    for B in (32, 33):
+    """A long contraction of I: the split kernels' bound, and down's row
+    groups of two, four and eight tiles."""
+    for B in (32, 33, 120, 400):
         run_case(gu, W.custom_layer(256, 5, 2, 2112, B, seed=97), 3)
+    run_case(gu, W.custom_layer(2048, 4, 2, 2112, 70, seed=97), 2)
 
 
 @pytest.mark.parametrize("B", [511, 513, 600])
