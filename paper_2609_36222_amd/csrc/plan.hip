@@ -24,12 +24,13 @@ namespace basek {
 
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_PAD = WAVE + 1;                 // LDS row of one chunk tree
-constexpr int SEL_V = 4 * 128 * SEL_PAD;          // chunk-matrix capacity (floats)
+constexpr int SEL_PAD4 = WAVE + 4;                // the same, read by four lanes a row: 16 rows on distinct banks
+constexpr int SEL_V = 4 * 128 * SEL_PAD4;         // chunk-matrix capacity (floats)
 
 // LDS of the selection (one workgroup of SEL_THREADS threads)
 struct SelLds {
   float V[SEL_V];
-  float CS[SEL_THREADS];
+  float CS[(MAX_B / WAVE) * MAX_E];   // chunk sums
   float D[MAX_E];
   int cnt[MAX_E];
   __attribute__((aligned(16))) uint64_t key[MAX_E];
@@ -37,67 +38,17 @@ struct SelLds {
   int n_union;
 };
 
-// Aggregation and selection by one workgroup of SEL_THREADS threads; thread
-// t < B brings token t's routes (uk) and costs (ck).  Chunk c (tokens 64c ..
-// 64c + 63) of expert u is the row V[c][u][0..63] (position j: the cost of
-// token 64c + j if it routes u, else +0); one thread per (chunk, expert)
-// adds its row by the halving tree, and the chunk sums are added to D_hat_u
-// in ascending chunk order.  The kept set is ranked with 64-bit keys whose
-// unsigned order is (D_hat desc, index asc) -- (D_hat > 0 desc, index asc)
-// with `binary`.  Writes scores, counts, sel_ids, n_sel and slot_of when
-// `out` is set, and slot_of into slot_lds when that is given; returns n_sel
-// (every thread).
-__device__ __forceinline__ int select_body(SelLds &S, int B, int K, int E, int budget,
-                                           int binary, const int (&uk)[MAX_K],
-                                           const float (&ck)[MAX_K], bool out,
+// The kept set from S.D and S.cnt: ranked with 64-bit keys whose unsigned order
+// is (D_hat desc, index asc) -- (D_hat > 0 desc, index asc) with `binary`.
+// Writes scores, counts, sel_ids, n_sel and slot_of when `out` is set, and
+// slot_of into slot_lds when that is given; returns n_sel (every thread).
+__device__ __forceinline__ int select_rank(SelLds &S, int E, int budget, int binary, bool out,
                                            float *__restrict__ scores,
                                            int32_t *__restrict__ counts,
                                            int32_t *__restrict__ sel_ids,
                                            int32_t *__restrict__ n_sel_out,
                                            int32_t *__restrict__ slot_of, int *slot_lds) {
   const int tid = threadIdx.x, lane = lane_id();
-  for (int u = tid; u < E; u += SEL_THREADS) { S.cnt[u] = 0; S.D[u] = 0.0f; }
-  if (tid == 0) S.n_union = 0;
-  const int nchunks = (B + WAVE - 1) / WAVE;
-  // chunks per batch: bounded by V and by one thread per (chunk, expert)
-  const int cb = max(1, min(min(nchunks, SEL_V / (E * SEL_PAD)), SEL_THREADS / E));
-  for (int c0 = 0; c0 < nchunks; c0 += cb) {
-    const int nb = min(cb, nchunks - c0);
-    const int nv = min(SEL_V, (nb * E * SEL_PAD + 3) & ~3) / 4;
-    for (int i = tid; i < nv; i += SEL_THREADS)
-      reinterpret_cast<float4 *>(S.V)[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};
-    __syncthreads();
-    // the routes in rank order (a repeated expert keeps its last cost, and
-    // counts every time)
-    const int cl = tid / WAVE - c0;
-    if (tid < B && cl >= 0 && cl < nb) {
-#pragma unroll
-      for (int k = 0; k < MAX_K; ++k)
-        if (k < K && uk[k] >= 0 && uk[k] < E) {
-          S.V[(cl * E + uk[k]) * SEL_PAD + lane] = ck[k];
-          atomicAdd(&S.cnt[uk[k]], 1);
-        }
-    }
-    __syncthreads();
-    if (tid < nb * E) {
-      // the tree's first level as the row is read (positions q, q + 32)
-      float v[WAVE / 2];
-#pragma unroll
-      for (int q = 0; q < WAVE / 2; ++q)
-        v[q] = S.V[tid * SEL_PAD + q] + S.V[tid * SEL_PAD + q + WAVE / 2];
-#pragma unroll
-      for (int h = WAVE / 4; h >= 1; h >>= 1)
-#pragma unroll
-        for (int q = 0; q < h; ++q) v[q] = v[q] + v[q + h];
-      S.CS[tid] = v[0];
-    }
-    __syncthreads();
-    for (int u = tid; u < E; u += SEL_THREADS)
-      for (int c = 0; c < nb; ++c)
-        S.D[u] = (c0 + c == 0) ? S.CS[c * E + u] : S.D[u] + S.CS[c * E + u];
-    __syncthreads();
-  }
-
   // E2: the power of two >= E (at least a wavefront); keys past E are 0
   int E2 = WAVE;
   while (E2 < E) E2 <<= 1;
@@ -159,6 +110,140 @@ __device__ __forceinline__ int select_body(SelLds &S, int B, int K, int E, int b
     if (tid == 0) *n_sel_out = n_sel;
   }
   return n_sel;
+}
+
+// Aggregation and selection by one workgroup of SEL_THREADS threads; thread
+// t < B brings token t's routes (uk) and costs (ck).  Chunk c (tokens 64c ..
+// 64c + 63) of expert u is the row V[c][u][0..63] (position j: the cost of
+// token 64c + j if it routes u, else +0); one thread per (chunk, expert)
+// adds its row by the halving tree, and the chunk sums are added to D_hat_u
+// in ascending chunk order; then the kept set (select_rank).
+__device__ __forceinline__ int select_body(SelLds &S, int B, int K, int E, int budget,
+                                           int binary, const int (&uk)[MAX_K],
+                                           const float (&ck)[MAX_K], bool out,
+                                           float *__restrict__ scores,
+                                           int32_t *__restrict__ counts,
+                                           int32_t *__restrict__ sel_ids,
+                                           int32_t *__restrict__ n_sel_out,
+                                           int32_t *__restrict__ slot_of, int *slot_lds) {
+  const int tid = threadIdx.x, lane = lane_id();
+  for (int u = tid; u < E; u += SEL_THREADS) { S.cnt[u] = 0; S.D[u] = 0.0f; }
+  if (tid == 0) S.n_union = 0;
+  const int nchunks = (B + WAVE - 1) / WAVE;
+  // chunks per batch: bounded by V and by one thread per (chunk, expert)
+  const int cb = max(1, min(min(nchunks, SEL_V / (E * SEL_PAD)), SEL_THREADS / E));
+  for (int c0 = 0; c0 < nchunks; c0 += cb) {
+    const int nb = min(cb, nchunks - c0);
+    const int nv = min(SEL_V, (nb * E * SEL_PAD + 3) & ~3) / 4;
+    for (int i = tid; i < nv; i += SEL_THREADS)
+      reinterpret_cast<float4 *>(S.V)[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+    __syncthreads();
+    // the routes in rank order (a repeated expert keeps its last cost, and
+    // counts every time)
+    const int cl = tid / WAVE - c0;
+    if (tid < B && cl >= 0 && cl < nb) {
+#pragma unroll
+      for (int k = 0; k < MAX_K; ++k)
+        if (k < K && uk[k] >= 0 && uk[k] < E) {
+          S.V[(cl * E + uk[k]) * SEL_PAD + lane] = ck[k];
+          atomicAdd(&S.cnt[uk[k]], 1);
+        }
+    }
+    __syncthreads();
+    if (tid < nb * E) {
+      // the tree's first level as the row is read (positions q, q + 32)
+      float v[WAVE / 2];
+#pragma unroll
+      for (int q = 0; q < WAVE / 2; ++q)
+        v[q] = S.V[tid * SEL_PAD + q] + S.V[tid * SEL_PAD + q + WAVE / 2];
+#pragma unroll
+      for (int h = WAVE / 4; h >= 1; h >>= 1)
+#pragma unroll
+        for (int q = 0; q < h; ++q) v[q] = v[q] + v[q + h];
+      S.CS[tid] = v[0];
+    }
+    __syncthreads();
+    for (int u = tid; u < E; u += SEL_THREADS)
+      for (int c = 0; c < nb; ++c)
+        S.D[u] = (c0 + c == 0) ? S.CS[c * E + u] : S.D[u] + S.CS[c * E + u];
+    __syncthreads();
+  }
+
+  return select_rank(S, E, budget, binary, out, scores, counts, sel_ids, n_sel_out, slot_of,
+                     slot_lds);
+}
+
+// The same aggregation for routes that are distinct within a token (the fused
+// layer's), the pairs taken flat: a pass zeroes its chunks of V while its pairs
+// are on their way, every thread scatters its own pairs, and four lanes per
+// (chunk, expert) add the row (lane p the positions p, p + 4, ..: the tree's
+// levels 32 to 4 are its own, 2 and 1 lane exchanges).  Thread-per-token routes
+// through LDS (load_routes) and one thread per row took, E = 128, K = 8, in us
+// for the launch: B = 128 8.1, B = 256 8.7, B = 1024 16.2; now 5.5, 6.4, 12.5
+// (with rows of 65 floats, four of sixteen rows on a bank: 6.2, 7.6, 17.1).
+__device__ __forceinline__ void aggregate_flat(SelLds &S, int B, int K, uint64_t kmul, int E,
+                                               const int32_t *__restrict__ ids,
+                                               const float *__restrict__ cost) {
+  constexpr int PP = 2;   // pairs per thread in flight
+  const int tid = threadIdx.x;
+  const int nchunks = (B + WAVE - 1) / WAVE, nq = B * K;
+  const int cb = max(1, min(nchunks, SEL_V / (E * SEL_PAD4)));   // chunks per pass
+  for (int u = tid; u < E; u += SEL_THREADS) S.cnt[u] = 0;
+  if (tid == 0) S.n_union = 0;
+  int u[PP];
+  float c[PP];
+  auto request = [&](int q) {
+#pragma unroll
+    for (int r = 0; r < PP; ++r) {
+      const int i = min(q + tid + r * SEL_THREADS, nq - 1);
+      u[r] = ids[i];
+      c[r] = cost[i];
+    }
+  };
+  request(0);
+  for (int c0 = 0; c0 < nchunks; c0 += cb) {
+    const int nb = min(cb, nchunks - c0);
+    const int q0 = c0 * WAVE * K, q1 = min(nq, (c0 + nb) * WAVE * K);
+    if (c0 > 0) __syncthreads();   // the previous pass's rows have been read
+    const int nv = min(SEL_V, (nb * E * SEL_PAD4 + 3) & ~3) / 4;
+    for (int i = tid; i < nv; i += SEL_THREADS)
+      reinterpret_cast<float4 *>(S.V)[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+    __syncthreads();
+    for (int g = q0; g < q1; g += PP * SEL_THREADS) {
+#pragma unroll
+      for (int r = 0; r < PP; ++r) {
+        const int i = g + tid + r * SEL_THREADS;
+        if (i < q1 && u[r] >= 0 && u[r] < E) {
+          const int t = (int)(((uint64_t)(uint32_t)i * kmul) >> 32);
+          S.V[((t / WAVE - c0) * E + u[r]) * SEL_PAD4 + t % WAVE] = c[r];
+          atomicAdd(&S.cnt[u[r]], 1);
+        }
+      }
+      // this pass's next pairs, or the next pass's first
+      request(g + PP * SEL_THREADS < q1 ? g + PP * SEL_THREADS : q1);
+    }
+    __syncthreads();
+    const int p = tid & 3;
+    for (int row = tid >> 2; row < nb * E; row += SEL_THREADS / 4) {
+      float v[WAVE / 4];
+#pragma unroll
+      for (int i = 0; i < WAVE / 4; ++i) v[i] = S.V[row * SEL_PAD4 + p + 4 * i];
+#pragma unroll
+      for (int h = WAVE / 8; h >= 1; h >>= 1)
+#pragma unroll
+        for (int i = 0; i < h; ++i) v[i] = v[i] + v[i + h];
+      float s = v[0];
+      s = s + xor_lane<2>(s);
+      s = s + xor_lane<1>(s);
+      if (p == 0) S.CS[c0 * E + row] = s;
+    }
+  }
+  __syncthreads();
+  for (int u = tid; u < E; u += SEL_THREADS) {
+    float D = S.CS[u];
+    for (int c = 1; c < nchunks; ++c) D = D + S.CS[c * E + u];
+    S.D[u] = D;   // read back by the same thread (select_rank) and at its end
+  }
 }
 
 // Thread t < B: token t's routes and costs (-1 / 0 past K; threads t >= B
@@ -394,7 +479,7 @@ void k_backfill(int B, int E, int K, int norm_topk, int flags,
 // execution order -- the values and the order of backfill_body.
 template <int NCH>
 __global__ __launch_bounds__(SEL_THREADS)
-void k_select_backfill(int B, int K, int E, int sbl, const int32_t *__restrict__ ids,
+void k_select_backfill(int B, int K, uint64_t kmul, int E, int sbl, const int32_t *__restrict__ ids,
                        const float *__restrict__ cost, int budget, int binary, int flags,
                        const uint8_t *__restrict__ order, const float *__restrict__ ex,
                        const float *__restrict__ den, float *__restrict__ scores,
@@ -422,11 +507,9 @@ void k_select_backfill(int B, int K, int E, int sbl, const int32_t *__restrict__
     xv[c] = active ? ex[(size_t)tc * E + r] : 0.0f;
   }
   const float dv = active ? den[tc] : 1.0f;
-  int uk[MAX_K];
-  float ck[MAX_K];
-  load_routes(B, K, ids, cost, S.V, uk, ck);
-  const int n_sel = select_body(S, B, K, E, budget, binary, uk, ck, blockIdx.x == 0, scores,
-                                counts, sel_ids, n_sel_out, slot_of, slot_s);
+  aggregate_flat(S, B, K, kmul, E, ids, cost);
+  const int n_sel = select_rank(S, E, budget, binary, blockIdx.x == 0, scores, counts, sel_ids,
+                                n_sel_out, slot_of, slot_s);
   __syncthreads();   // slot_s complete
   if (!active || t >= B) return;
   const int kp = min(K, n_sel);
@@ -1022,9 +1105,9 @@ void k_plan_split(int B, int K, int E, int budget, int ns, int binary, int flags
                   int32_t *__restrict__ pair_tok, float *__restrict__ pair_gate,
                   int32_t *__restrict__ pair_of, SpRec *__restrict__ rec,
                   int32_t *__restrict__ sptok) {
-  constexpr int PL_PAD = PL_T + 1;
+  constexpr int PL_PAD = PL_T + 4;   // four lanes a row: 16 rows on distinct banks
   constexpr int TPW = PL_T / (PL_THREADS / WAVE);   // tokens per wavefront
-  __shared__ float V[MAX_E * PL_PAD];
+  __shared__ __attribute__((aligned(16))) float V[MAX_E * PL_PAD];
   __shared__ int cnt[MAX_E];
   __shared__ __attribute__((aligned(16))) uint64_t key[MAX_E];
   __shared__ int slot_s[MAX_E], sel_s[MAX_E];
@@ -1053,7 +1136,8 @@ void k_plan_split(int B, int K, int E, int budget, int ns, int binary, int flags
   }
   const float gd = gdot ? gdot[min(tid, B - 1)] : 0.0f;
   const int t_r = tid / K;
-  for (int i = tid; i < E * PL_PAD; i += PL_THREADS) V[i] = 0.0f;
+  for (int i = tid; i < E * PL_PAD / 4; i += PL_THREADS)
+    reinterpret_cast<float4 *>(V)[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};
   if (tid < E) {
     cnt[tid] = 0;
     mask[tid] = 0ull;
@@ -1300,9 +1384,10 @@ hipError_t launch_select_backfill(int B, int K, int E, const int32_t *ids, const
                                   int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
                                   int n_cu, hipStream_t st) {
   const int sbl = sb_tokens_log2(B, n_cu);
+  const uint64_t kmul = ((1ull << 32) + (uint64_t)K - 1) / (uint64_t)K;   // t = q / K as in k_compact
   const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP >> sbl));
 #define BASE_SB(C)                                                                         \
-  launch_k(k_select_backfill<C>, grid, dim3(SEL_THREADS), 0, st, B, K, E, sbl, ids, cost, budget, \
+  launch_k(k_select_backfill<C>, grid, dim3(SEL_THREADS), 0, st, B, K, kmul, E, sbl, ids, cost, budget, \
            (int)binary, flags, order, ex, den, scores, counts, sel_ids, n_sel, slot_of,     \
            exec_ids, exec_gates)
   if (E <= WAVE) BASE_SB(1);
