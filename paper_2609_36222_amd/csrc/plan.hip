@@ -656,6 +656,29 @@ __device__ __forceinline__ void wave_scan_counts(const int *cnt, int *pre) {
   if (lane == WAVE - 1) pre[SCAN_N] = inc;
 }
 
+// First position of die y when n slots are dealt to the dies whole: die z holds
+// ceil((n - z) / N_XCD) of them.
+__device__ __forceinline__ int deal_first(int n, int y) {
+  return y * (n / N_XCD) + min(y, n % N_XCD);
+}
+static_assert(N_XCD == 8, "min8 / max8 over a die's lane each");
+// Minimum and maximum over each group of 8 lanes (quad permutations, then the
+// half-row mirror).
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int min8(int v) {
+  v = min(v, dpp<0xB1>(v));
+  v = min(v, dpp<0x4E>(v));
+  return min(v, dpp<0x141>(v));
+}
+__device__ __forceinline__ int max8(int v) {
+  v = max(v, dpp<0xB1>(v));
+  v = max(v, dpp<0x4E>(v));
+  return max(v, dpp<0x141>(v));
+}
+
 constexpr int CP_THREADS = 1024;
 constexpr int CP_WAVES = CP_THREADS / WAVE;
 constexpr int CP_STAGE = 4096;   // pair gates staged in LDS per pass
@@ -823,8 +846,7 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
         // slot r / N_XCD; die y holds ceil((nslot - y) / N_XCD) slots
         const bool multi = hr[s + 1] > hr[s];
         const int r = multi ? hr[s] : hr[SCAN_N] + (s - hr[s]), y = r % N_XCD;
-        j = r / N_XCD;
-        for (int z = 0; z < y; ++z) j += (nslot - z + N_XCD - 1) / N_XCD;
+        j = r / N_XCD + deal_first(nslot, y);
       }
       const int nt = tb[s + 1] - tb[s];
       const PartSplit sg = part_split(nt, FFN_GU_PT);
@@ -863,25 +885,27 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
     const int x = blockIdx.x;
     const int T = I / 16, Pg = pre_gu[SCAN_N], Pd = pre_dn[SCAN_N];
     const float per_die = (float)(ffn_gu_grid(n_cu) / N_XCD);
+    // (one candidate per lane, the choice over the 8 lanes: a loop over the
+    // candidates cost 16 wavefronts 1 us)
+    const int l8 = lane & 7;
+    // ceil(units / workgroups of a die)
+    auto rounds = [](int units, float wgs) { return (int)ceilf((float)units / wgs); };
     // parts on the busiest die: dealt slots, or an even share
-    int pmax = (Pg + N_XCD - 1) / N_XCD;
-    if (whole) {
-      pmax = 0;
-      for (int y = 0, j = 0; y < N_XCD; ++y) {
-        const int jn = j + (nslot - y + N_XCD - 1) / N_XCD;
-        pmax = max(pmax, pre_gu[jn] - pre_gu[j]);
-        j = jn;
-      }
-    }
-    int rp = FFN_WAVES, best_cost = 0x7FFFFFFF;
-    for (int c = FFN_WAVES; c >= FFN_WAVES / 2; --c) {
-      // the busiest die's units: its dealt parts' row groups, or an equal
-      // share of all of them
-      const int units = whole ? pmax * ((T + c - 1) / c)
-                              : (Pg * ((T + c - 1) / c) + N_XCD - 1) / N_XCD;
-      // rounds = ceil(units / per_die); exact in fp32 for these small integers
-      const int cost = (int)ceilf((float)units / per_die) * c;
-      if (cost < best_cost) { rp = c; best_cost = cost; }
+    auto busiest = [&](const int *pre, int parts) {
+      return whole ? max8(pre[deal_first(nslot, l8 + 1)] - pre[deal_first(nslot, l8)])
+                   : (parts + N_XCD - 1) / N_XCD;
+    };
+    // the busiest die's units: its dealt parts' row groups, or an equal share
+    // of all of them
+    auto units_of = [&](int pmax, int parts, int upp) {
+      return whole ? pmax * upp : (parts * upp + N_XCD - 1) / N_XCD;
+    };
+    const int pmax = busiest(pre_gu, Pg);
+    int rp;   // FFN_WAVES down to FFN_WAVES / 2 row-pair tiles; ties: the larger group
+    {
+      const int c = FFN_WAVES - l8;
+      const int cost = rounds(units_of(pmax, Pg, (T + c - 1) / c), per_die) * c;
+      rp = FFN_WAVES - (min8(c >= FFN_WAVES / 2 ? cost << 3 | l8 : 0x7FFFFFFF) & 7);
     }
     // down's row group: FFN_WAVES row tiles, or for a long contraction (one
     // workgroup per CU) fewer when that gives the busiest workgroup less to
@@ -894,23 +918,10 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
     const int Td = d / 16;
     int rd = FFN_WAVES;
     if (ffn_dn_long(I)) {
-      int pdmax = (Pd + N_XCD - 1) / N_XCD;
-      if (whole) {
-        pdmax = 0;
-        for (int y = 0, j = 0; y < N_XCD; ++y) {
-          const int jn = j + (nslot - y + N_XCD - 1) / N_XCD;
-          pdmax = max(pdmax, pre_dn[jn] - pre_dn[j]);
-          j = jn;
-        }
-      }
-      const float wgs = (float)(ffn_dn_grid(n_cu, 2) / N_XCD);
-      int best = 0x7FFFFFFF;
-      for (int c = FFN_WAVES; c >= 2; c /= 2) {
-        const int units = whole ? pdmax * ((Td + c - 1) / c)
-                                : (Pd * ((Td + c - 1) / c) + N_XCD - 1) / N_XCD;
-        const int cost = (int)ceilf((float)units / wgs) * (c * Pd + tb[SCAN_N]);
-        if (cost < best) { rd = c; best = cost; }
-      }
+      const int c = max(FFN_WAVES >> l8, 1);
+      const int units = units_of(busiest(pre_dn, Pd), Pd, (Td + c - 1) / c);
+      const int cost = rounds(units, (float)(ffn_dn_grid(n_cu, 2) / N_XCD)) * (c * Pd + tb[SCAN_N]);
+      rd = FFN_WAVES >> (min8(c >= 2 ? cost << 3 | l8 : 0x7FFFFFFF) & 7);
     }
     const int ug = (T + rp - 1) / rp, ud = (Td + rd - 1) / rd;
     // die y's first unit in both tables and first position.  Whole slots:
@@ -921,9 +932,7 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
     int g0, g1, d0, d1, s0, s1;   // this die's runs; their positions lie in [s0, s1]
     if (whole) {
       // every thread finds its own die's first positions
-      int j0 = 0;
-      for (int z = 0; z < x; ++z) j0 += (nslot - z + N_XCD - 1) / N_XCD;
-      const int j1 = j0 + (nslot - x + N_XCD - 1) / N_XCD;
+      const int j0 = deal_first(nslot, x), j1 = deal_first(nslot, x + 1);
       g0 = pre_gu[j0] * ug; g1 = pre_gu[j1] * ug;
       d0 = pre_dn[j0] * ud; d1 = pre_dn[j1] * ud;
       s0 = min(j0, nslot - 1); s1 = min(j1, nslot - 1);
@@ -961,31 +970,28 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
       h.pad1 = h.pad2 = 0;
       hdr[x] = h;
     }
-    // unit i: its position (the first j with pre[j + 1] * upp > i) and
-    // slot, then row group and part
-    auto put_unit = [&](int i, int upp, const int *pre, const int *np, int pt, FfnUnit *dst) {
-      int lo = s0, hi = s1;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (pre[mid + 1] * upp > i) hi = mid; else lo = mid + 1;
+    // the units [i0, i1) of a table, a wavefront per position j: the slot, then
+    // each unit's row group and part
+    auto put_units = [&](int i0, int i1, int upp, const int *pre, const int *np, int pt,
+                         FfnUnit *dst) {
+      for (int j = s0 + wv; j <= s1; j += CP_WAVES) {
+        const int base = pre[j] * upp, last = min(i1, pre[j + 1] * upp);
+        if (max(i0, base) >= last) continue;
+        const int s = slot_at[j], npj = np[j], tbs = tb[s], offs = off[s], n = cnt[s];
+        const PartSplit sp = part_split(tb[s + 1] - tbs, pt);
+        const int u = s < n_sel ? sel_s[s] : E + (s - n_sel);
+        for (int i = max(i0, base) + lane; i < last; i += WAVE) {
+          const int r = i - base;
+          const int dv = whole ? upp : npj, qt = r / dv, rm = r - qt * dv;
+          const int rg = whole ? rm : qt, q = whole ? qt : rm;
+          const int c = q < sp.ex ? sp.lo + 1 : sp.lo;
+          const int tf = q * sp.lo + min(q, sp.ex);   // the part's first tile in its slot
+          dst[i] = FfnUnit{u, tbs + tf, c, offs + 16 * tf, min(16 * c, n - 16 * tf), rg, 0, 0};
+        }
       }
-      const int j = lo, s = slot_at[j], r = i - pre[j] * upp;
-      const int rg = whole ? r % upp : r / np[j], q = whole ? r / upp : r % np[j];
-      const PartSplit sp = part_split(tb[s + 1] - tb[s], pt);
-      const int c = q < sp.ex ? sp.lo + 1 : sp.lo;
-      const int tf = q * sp.lo + min(q, sp.ex);   // the part's first tile in its slot
-      FfnUnit rec;
-      rec.u = s < n_sel ? sel_s[s] : E + (s - n_sel);
-      rec.tile0 = tb[s] + tf;
-      rec.nt = c;
-      rec.p0 = off[s] + 16 * tf;
-      rec.n = min(16 * c, cnt[s] - 16 * tf);
-      rec.rg = rg;
-      rec.pad0 = rec.pad1 = 0;
-      dst[i] = rec;
     };
-    for (int i = g0 + tid; i < g1; i += CP_THREADS) put_unit(i, ug, pre_gu, np_gu, FFN_GU_PT, units_gu);
-    for (int i = d0 + tid; i < d1; i += CP_THREADS) put_unit(i, ud, pre_dn, np_dn, FFN_DN_PT, units_dn);
+    put_units(g0, g1, ug, pre_gu, np_gu, FFN_GU_PT, units_gu);
+    put_units(d0, d1, ud, pre_dn, np_dn, FFN_DN_PT, units_dn);
     // gate/up's token row of pair pr of slot s (token t), in every unit of
     // its part in [g0, g1).  The
     // part of tile ti: the first ex parts have lo + 1 tiles, the others lo;
