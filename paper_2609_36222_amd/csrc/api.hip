@@ -152,8 +152,9 @@ Layout layout(const base_layer *L, int32_t B, int32_t bc) {
   // (small batches: gate/up's token lists, one per die, lie here until down
   // writes its rows)
   o.pairbuf = take(P * L->d * 4);
-  static_assert(MAX_E <= 256 && SC_SMALL_B <= 2 * 16 * 64 / 4,
-                "q [B][E] in B rows of d >= 256 floats, ss [B] in one activation tile");
+  // (q [B][E] of the dense scores fits: E <= 256 <= d; ||x||^2 [B] in the
+  // activations: B K / 16 tiles of 16 I 2 bytes with I >= 64, or B K I 4 bytes)
+  static_assert(MAX_E <= 256, "q in the pair rows' buffer");
   o.total = at;
   return o;
 }
@@ -443,7 +444,7 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
   stage(0, st);
   // a small batch's launch also makes the predictor's dot products: q lies in
   // the pair rows' buffer and ||x||^2 in the activations', free until the FFN
-  const bool dense = scores_small(B) && L->score_rule == BASE_SCORE_BASE;
+  const bool dense = scores_small(B, L->E) && L->score_rule == BASE_SCORE_BASE;
   float *qd = dense ? at<float>(ws, o.pairbuf) : nullptr, *ss = dense ? at<float>(ws, o.H) : nullptr;
   HIP_TRY(launch_scores(bf16, x, B, L->d, L->w_router, L->b_router, L->E, shared_gate(L),
                         logits, at<float>(ws, o.gdot), st, dense ? L->pred_a : nullptr, qd, ss));

@@ -172,8 +172,8 @@ __host__ __device__ inline unsigned ffn_dn_grid(int n_cu, int kind) {
 // scores_small batches may also take the predictor's rows A [n_router]: the
 // dot products of every expert (q [B][n_router]) and ||x||^2 (ss [B]); where
 // the line lies: k_scores_small
-constexpr int SC_SMALL_B = 64;
-inline bool scores_small(int B) { return B <= SC_SMALL_B; }
+constexpr int SC_SMALL_B = 64, SC_SMALL_DOTS = 64 * 128;
+inline bool scores_small(int B, int E) { return B <= SC_SMALL_B || B * E <= SC_SMALL_DOTS; }
 hipError_t launch_scores(bool bf16, const void *x, int B, int d, const float *Wr,
                          const float *beta, int n_router, const float *G, float *logits,
                          float *gdot, hipStream_t st, const float *A = nullptr,

@@ -215,7 +215,7 @@ void k_scores(const XT *__restrict__ x, int B, int d,
   }
 }
 
-// Small batches (B <= SC_SMALL_B).  The tiled kernel's few workgroups (16 at B
+// Few dot products (scores_small).  The tiled kernel's few workgroups (16 at B
 // <= 16, on one die) walk their chunks behind LDS barriers; here a wavefront
 // takes 4 tokens x 4 rows straight into registers, SS_GC chunks of 256
 // elements at a time with the next ones in flight, and nothing is shared, so
@@ -225,15 +225,19 @@ void k_scores(const XT *__restrict__ x, int B, int d,
 // the routing is known.  Each dot product in the fixed order.
 // A workgroup is 4 wavefronts: 16 tokens (a token group) x 4 rows.  The router
 // rows of token group g run on die g % N_XCD, where k_tail reads the logits;
-// the predictor's and the extra rows (G; x itself) on the other dies: workgroup
-// b on die b % N_XCD is number b / N_XCD there.
+// the predictor's and the extra rows (G; x itself) on the dies without a token
+// group, or, past N_XCD / 2 groups, on the group's own: workgroup b on die b %
+// N_XCD is number b / N_XCD there.
 // Scores + tail, against the tiled kernel and the predictor in the tail (E =
 // 128, d = 2048, us): B = 1 7.6 + 5.1 -> 4.8 + 4.0, B = 16 7.8 + 5.5 -> 5.7 + 4.0,
 // B = 64 8.0 + 5.6 -> 7.6 + 4.0; E = 8, d = 4096, B = 16 13.3 + 4.8 -> 9.0 +
-// 4.0.  Beyond 64 tokens the unshared reads (48 KB a wavefront) catch up with
-// what the tiles save.  Four chunks at a time: equal, slower at d = 256.
+// 4.0.  The line, B <= 64 or B E <= 64 * 128: beyond, the unshared reads (48 KB a
+// wavefront) catch up with what the tiles save (E = 128: layer at B = 80 66.4
+// tiled, 67.7 here; B = 128 87.8, 87.2; B = 256 111, 115), below they gain (E =
+// 64: B = 72 76.9 -> 73.8, B = 128 84.2 -> 81.4; E = 8, d = 4096: B = 128 299.7
+// -> 293.6, B = 1000 1041 -> 1036).  Four chunks at a time: equal, slower at d =
+// 256.
 constexpr int SS_GC = 2;
-static_assert(SC_SMALL_B / TOK_GROUP < N_XCD, "a die left for the predictor's rows");
 
 template <typename XT>
 __global__ __launch_bounds__(4 * WAVE, 2)
@@ -245,17 +249,22 @@ void k_scores_small(const XT *__restrict__ x, int B, int d, const float *__restr
   const int lane = lane_id(), w = wave_id_u();
   const int die = blockIdx.x % N_XCD, nb = blockIdx.x / N_XCD;
   const int rgs = (E + 3) / 4;   // row groups of 4
+  const int per = n_other / n_group;   // a token group's others: predictor groups, one of extras
   int g, rg;
-  const bool router = die < n_group;
-  if (router) {
+  bool router = die < n_group;
+  if (n_group > N_XCD / 2) {
+    const int q = nb / (rgs + per);
+    g = die + N_XCD * q;
+    rg = nb - q * (rgs + per);
+    router = rg < rgs;
+    if (!router) rg -= rgs;
+  } else if (router) {
     g = die;
     rg = nb;
     if (rg >= rgs) return;
   } else {
-    // the rest, token group by token group: pgs predictor groups, one of extras
     const int i = nb * (N_XCD - n_group) + die - n_group;
     if (i >= n_other) return;
-    const int per = n_other / n_group;
     g = i / per;
     rg = i - g * per;
   }
@@ -583,11 +592,17 @@ template <typename XT>
 static void launch_scores_t(const XT *x, int B, int d, const float *Wr, const float *beta,
                             int n_router, const float *G, float *logits, float *gdot,
                             const float *A, float *q, float *ss, hipStream_t st) {
-  if (scores_small(B)) {
+  if (scores_small(B, n_router)) {
     const int n_group = (B + TOK_GROUP - 1) / TOK_GROUP, rgs = (n_router + 3) / 4;
     const int n_other = n_group * ((A ? rgs : 0) + (A || G ? 1 : 0));
-    const int dies = N_XCD - n_group, nb = (n_other + dies - 1) / dies;
-    launch_k(k_scores_small<XT>, dim3(N_XCD * (rgs > nb ? rgs : nb)), dim3(4 * WAVE), 0, st, x, B,
+    int nb;   // workgroups per die
+    if (n_group > N_XCD / 2) {
+      nb = (n_group + N_XCD - 1) / N_XCD * (rgs + n_other / n_group);
+    } else {
+      const int dies = N_XCD - n_group, no = (n_other + dies - 1) / dies;
+      nb = rgs > no ? rgs : no;
+    }
+    launch_k(k_scores_small<XT>, dim3(N_XCD * nb), dim3(4 * WAVE), 0, st, x, B,
              d, Wr, beta, n_router, A, G, n_group, n_other, logits, q, ss, gdot);
     return;
   }

@@ -89,6 +89,17 @@ def test_fp32_rows(gu, B, d, I):  # noqa: F811
 @pytest.mark.parametrize("d,E,bf16,sg", [(256, 3, True, 1), (768, 37, False, 0), (1024, 256, True, 0),
                                          (2304, 8, True, 1)])
 def test_small_scores(gu, B, d, E, bf16, sg):  # noqa: F811
+    _small_scores(gu, B, d, E, bf16, sg)
+
+
+@pytest.mark.parametrize("B,E", [(81, 100), (82, 100), (100, 64), (128, 64), (129, 64), (1000, 8),
+                                 (300, 3)])
+def test_small_scores_of_many_tokens(gu, B, E):  # noqa: F811
+    """More token groups than dies: every row of a group on its own die."""
+    _small_scores(gu, B, 512, E, True, 1)
+
+
+def _small_scores(gu, B, d, E, bf16, sg):  # noqa: F811
     """Router, predictor and extra rows in one launch: token and row
     remainders, chunks of the contraction that do not fill a pass."""
     inp = W.custom_layer(d, E, min(E, 5), 64, B, bf16=bf16, seed=98, n_shared=sg,
