@@ -354,9 +354,10 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
  * the pair is that kernel's execution time, with nothing added to the
  * stream between kernels.  A stage that launches no kernel (stage 5
  * always) records its pair back to back.
- * Stages: 0 scores (router logits, the shared experts' gate dots), 1 tail
- * (top-K, router weights, the routed pairs' predictor dot products, norms
- * and predicted costs), 2 aggregation + selection,
+ * Stages: 0 scores (router logits, the shared experts' gate dots; with few
+ * dot products also the predictor's, for every expert, and the norms), 1 tail
+ * (top-K, router weights, otherwise the routed pairs' predictor dot products
+ * and norms, and predicted costs), 2 aggregation + selection,
  * 3 backfill + gates, 4 compaction and the FFN's part tables, 5 (no
  * kernel: FFN gate/up gathers its own token rows), 6 FFN gate/up, 7 FFN
  * down, 8 combine.  base_route runs stages 0 and 1,

@@ -132,3 +132,34 @@ def test_long_contraction(gu):  # noqa: F811
 def test_selection_workgroups(gu, B):  # noqa: F811
     """Where the fused selection takes more tokens per workgroup."""
     run_case(gu, W.custom_layer(256, 24, 3, 64, B, seed=90), 7)
+
+
+@pytest.mark.parametrize("B", [3, 130])
+def test_graph_replay_either_side_of_the_line(gu, B):  # noqa: F811
+    """A captured layer on the small batches' launches and on the general
+    ones: replays on new tokens, over a workspace of junk, equal eager calls
+    bit for bit."""
+    from paper_2609_36222_amd import binding as bd
+    inp = W.custom_layer(512, 32, 4, 128, B, seed=99, n_shared=1, shared_gate=True)
+    gl = gu.GpuLayer(inp, packed=True)
+    xs = [gl.x(W.decode_tokens(inp["shape"], 0, data_seed=s)) for s in range(3)]
+    x, ws, y = xs[0].clone(), gl.workspace(B, 9), gl.y_like(B)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        bd.base_decode_layer(gl.desc, x, B, 9, 0, None, y, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bd.base_decode_layer(gl.desc, x, B, 9, 0, None, y, ws)
+    for rep in range(5):
+        xk, ws_e, y_e = xs[rep % 3], gl.workspace(B, 9), gl.y_like(B)
+        bd.base_decode_layer(gl.desc, xk, B, 9, 0, None, y_e, ws_e)
+        x.copy_(xk)
+        ws.fill_(0xA5)
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(gu.to_np_f32(y), gu.to_np_f32(y_e)), rep
