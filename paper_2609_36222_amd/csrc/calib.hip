@@ -275,6 +275,39 @@ __device__ __forceinline__ f32x4 mfma_bf16_32(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// Rows cb + 4 m + b, columns rb + 16 kk + 4 r .. + 3 get v[r][0..3][b]: a
+// quarter's mirror.  Stored as held, every lane of an instruction has a 64-byte
+// segment of its own; so the lanes m % 4 first exchange pieces r, and four
+// neighbours then store 64 contiguous bytes (two batches of 1024 OLMoE-shaped
+// tokens from zero 1710 -> 1607 us).
+template <int H>
+__device__ __forceinline__ void swap_piece(f32x4 &lo, f32x4 &hi, bool odd) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float got = xor_lane<H>(odd ? lo[e] : hi[e]);
+    lo[e] = odd ? got : lo[e];
+    hi[e] = odd ? hi[e] : got;
+  }
+}
+__device__ __forceinline__ void store_mirror(float *g, int d, int rb, int cb, int m, int kk,
+                                             const f32x4 (&v)[4][4]) {
+  const int q = m & 3;
+  float *to = g + (size_t)(cb + 4 * (m - q)) * d + rb + 16 * kk + 4 * q;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    f32x4 t[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[r] = f32x4{v[r][0][b], v[r][1][b], v[r][2][b], v[r][3][b]};
+    swap_piece<1>(t[0], t[1], q & 1);
+    swap_piece<1>(t[2], t[3], q & 1);
+    swap_piece<2>(t[0], t[2], q & 2);
+    swap_piece<2>(t[1], t[3], q & 2);
+    // t[i]: piece q of the row that lane m - q + i held
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(f32x4 *)(to + (size_t)(4 * i + b) * d) = t[i];
+  }
+}
+
 __global__ __launch_bounds__(GM_WAVES * WAVE, 2)
 void k_calib_gram(const float *__restrict__ zbuf, int B, int d, int n_blk, int slots_per_die,
                   const int32_t *__restrict__ n_sel, const int32_t *__restrict__ sel_ids,
@@ -344,14 +377,7 @@ void k_calib_gram(const float *__restrict__ zbuf, int B, int d, int n_blk, int s
       *(f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m) = v;
       old[r][a] = v;
     }
-  if (I != J) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        *(f32x4 *)(g + (size_t)(cb + 4 * m + b) * d + rb + 16 * kk + 4 * r) =
-            f32x4{old[r][0][b], old[r][1][b], old[r][2][b], old[r][3][b]};
-  }
+  if (I != J) store_mirror(g, d, rb, cb, m, kk, old);
 }
 
 // bf16 layers: the same blocks, quarters and tiles, on the bf16 matrix
@@ -499,12 +525,7 @@ void k_calib_gram_bf16(GramRows gr, int B, int d, int n_blk, int slots_per_die,
       *(f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m) = v;
       old[r][a] = v;
     }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-      *(f32x4 *)(g + (size_t)(cb + 4 * m + b) * d + rb + 16 * kk + 4 * r) =
-          f32x4{old[r][0][b], old[r][1][b], old[r][2][b], old[r][3][b]};
+  store_mirror(g, d, rb, cb, m, kk, old);
 }
 
 __global__ __launch_bounds__(CAL_THREADS)
