@@ -27,6 +27,28 @@ namespace basek {
 constexpr int CAL_THREADS = 256;
 constexpr double CAL_EPS = 1e-12;
 
+// A 16-byte load and store of the statistics; STREAM: past the caches' usual
+// replacement (non-temporal).
+template <bool STREAM>
+__device__ __forceinline__ f32x4 load_g(const float *p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+  return *reinterpret_cast<const f32x4 *>(p);
+}
+template <bool STREAM>
+__device__ __forceinline__ void store_g(float *p, f32x4 v) {
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
+  else
+    *reinterpret_cast<f32x4 *>(p) = v;
+}
+// Gram matrices larger than the 256 MB Infinity Cache are gone from it before
+// the next batch reads them, and as they pass they push out the token rows:
+// non-temporal then (OLMoE-shaped, 1.07 GB, two batches from zero 1610 -> 1517
+// us; d = 1280, E = 48, 315 MB, one batch 247 -> 240).  Smaller ones are found
+// there again (d = 1024, E = 32, 134 MB, two batches: 279 us, 292
+// non-temporal).
+constexpr size_t G_STREAM_BYTES = (size_t)256 << 20;
+
 // Elements c, c + 1 of an activation row.
 __device__ __forceinline__ double2 act2(const void *row, bool bf16, int c) {
   if (bf16) {
@@ -289,6 +311,7 @@ __device__ __forceinline__ void swap_piece(f32x4 &lo, f32x4 &hi, bool odd) {
     hi[e] = odd ? hi[e] : got;
   }
 }
+template <bool STREAM>
 __device__ __forceinline__ void store_mirror(float *g, int d, int rb, int cb, int m, int kk,
                                              const f32x4 (&v)[4][4]) {
   const int q = m & 3;
@@ -304,7 +327,7 @@ __device__ __forceinline__ void store_mirror(float *g, int d, int rb, int cb, in
     swap_piece<2>(t[1], t[3], q & 2);
     // t[i]: piece q of the row that lane m - q + i held
 #pragma unroll
-    for (int i = 0; i < 4; ++i) *(f32x4 *)(to + (size_t)(4 * i + b) * d) = t[i];
+    for (int i = 0; i < 4; ++i) store_g<STREAM>(to + (size_t)(4 * i + b) * d, t[i]);
   }
 }
 
@@ -377,7 +400,7 @@ void k_calib_gram(const float *__restrict__ zbuf, int B, int d, int n_blk, int s
       *(f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m) = v;
       old[r][a] = v;
     }
-  if (I != J) store_mirror(g, d, rb, cb, m, kk, old);
+  if (I != J) store_mirror<false>(g, d, rb, cb, m, kk, old);
 }
 
 // bf16 layers: the same blocks, quarters and tiles, on the bf16 matrix
@@ -407,6 +430,7 @@ __device__ __forceinline__ bf16x8 halves8(const u32x2 (&r)[8], int c) {
   return __builtin_bit_cast(bf16x8, f);
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(GM_WAVES * WAVE, 2)
 void k_calib_gram_bf16(GramRows gr, int B, int d, int n_blk, int slots_per_die,
                        const int32_t *__restrict__ n_sel, const int32_t *__restrict__ sel_ids,
@@ -499,7 +523,7 @@ void k_calib_gram_bf16(GramRows gr, int B, int d, int n_blk, int slots_per_die,
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int a = 0; a < 4; ++a)
-      old[r][a] = *(const f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m);
+      old[r][a] = load_g<STREAM>(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m);
 
   if (rb == cb) {
     // a diagonal quarter: i <= j, mirrored
@@ -522,10 +546,10 @@ void k_calib_gram_bf16(GramRows gr, int B, int d, int n_blk, int slots_per_die,
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const f32x4 v = old[r][a] + f32x4{acc[a][0][r], acc[a][1][r], acc[a][2][r], acc[a][3][r]};
-      *(f32x4 *)(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m) = v;
+      store_g<STREAM>(g + (size_t)(rb + 16 * kk + 4 * r + a) * d + cb + 4 * m, v);
       old[r][a] = v;
     }
-  store_mirror(g, d, rb, cb, m, kk, old);
+  store_mirror<STREAM>(g, d, rb, cb, m, kk, old);
 }
 
 __global__ __launch_bounds__(CAL_THREADS)
@@ -564,7 +588,9 @@ hipError_t launch_calib_stats(const void *x, bool bf16, int B, int d, int E, int
   const int per_die = (E + N_XCD - 1) / N_XCD;
   const dim3 grid((unsigned)(N_XCD * per_die * n_blk));
   if (bf16)
-    launch_k(k_calib_gram_bf16, grid, dim3(GM_WAVES * WAVE), 0, s, gr, B, d, n_blk, per_die, n_sel, sel_ids, offsets, pair_tok, st.G);
+    launch_k((size_t)E * d * d * 4 > G_STREAM_BYTES ? k_calib_gram_bf16<true> : k_calib_gram_bf16<false>,
+             grid, dim3(GM_WAVES * WAVE), 0, s, gr, B, d, n_blk, per_die, n_sel, sel_ids, offsets,
+             pair_tok, st.G);
   else
     launch_k(k_calib_gram, grid, dim3(GM_WAVES * WAVE), 0, s, (const float *)zbuf, B, d, n_blk,
              per_die, n_sel, sel_ids, offsets, pair_tok, st.G);
