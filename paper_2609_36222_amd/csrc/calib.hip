@@ -415,8 +415,9 @@ void k_calib_gram(const float *__restrict__ zbuf, int B, int d, int n_blk, int s
 // planes of v instead: 643 against 451 us, the row reads then bound it).
 // G's old values are read after the contraction: held across it (as in the fp32
 // kernel) they spill, 473 against 420 us per batch of 1024 OLMoE-shaped tokens
-// (1.6 GB of G moved, 3.8 TB/s; without the contraction 313).  The fp32
-// kernel took 548.
+// (before the mirror's 64-byte stores and non-temporal access; without the
+// contraction 313 then).  The fp32 kernel took 548; now 365 (1.6 GB of G moved,
+// 4.4 TB/s), traced on a box whose other kernels ran up to a tenth longer.
 // The two sides are not alike, so inside a diagonal 64 x 64 quarter the
 // elements above the diagonal are kept and mirrored, and the quarter below
 // the diagonal of a diagonal block is the mirror of the one above: G_u stays
