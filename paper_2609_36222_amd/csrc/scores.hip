@@ -219,10 +219,15 @@ void k_scores(const XT *__restrict__ x, int B, int d,
 // <= 16, on one die) walk their chunks behind LDS barriers; here a wavefront
 // takes 4 tokens x 4 rows straight into registers, SS_GC chunks of 256
 // elements at a time with the next ones in flight, and nothing is shared, so
-// the launch is one memory latency, 256 FMAs and a tree.  With the chip
+// the launch is a ring of loads (d = 2048: four stages, two of them in flight
+// at once), 64 FMAs a chunk and a tree.  With the chip
 // otherwise idle it also makes the predictor's dot products with every
 // expert (A, q) and ||x||^2 (ss), which k_tail would otherwise start only once
-// the routing is known.  Each dot product in the fixed order.
+// the routing is known.  Each dot product in the fixed order.  The extra rows
+// go through the same ring (as a plain loop, one round trip a chunk, they were
+// the launch's longest wavefronts: the Mixtral-shaped d = 4096 layer with a
+// gate, staged at B = 16, 27.2 us, now 26.6; d = 16384 at B = 1 48.6 and 46.4,
+// the whole layer 65.1 and 58.1).
 // A workgroup is 4 wavefronts: 16 tokens (a token group) x 4 rows.  The router
 // rows of token group g run on die g % N_XCD, where k_tail reads the logits;
 // the predictor's and the extra rows (G; x itself) on the dies without a token
@@ -282,64 +287,76 @@ void k_scores_small(const XT *__restrict__ x, int B, int d, const float *__restr
   float acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-  if (extra) {   // rows: 0 x itself, 1 G
-    for (int m = 0; m < d; m += 256) {
-      float gv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (G) load4(wr[0] + m, gv);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        float xv[4];
-        load4(xr[a] + m, xv);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          acc[4 * a] = __builtin_fmaf(xv[r], xv[r], acc[4 * a]);
-          acc[4 * a + 1] = __builtin_fmaf(xv[r], gv[r], acc[4 * a + 1]);
-        }
-      }
-    }
-  } else {
-    Raw4<XT> xv[2][SS_GC][4];
-    float4 wv[2][SS_GC][4];
+  // the rows' chunks through a ring of two stages of SS_GC chunks: load(s, c, m)
+  // requests the matrix rows of the chunk at element m, use(s, c) adds it
+  Raw4<XT> xv[2][SS_GC][4];
+  float4 wv[2][SS_GC][4];
+  auto stream = [&](auto load, auto use) {
     auto fetch = [&](int s, int m0) {
 #pragma unroll
       for (int c = 0; c < SS_GC; ++c) {
         const int m = min(m0 + 256 * c, d - 256);   // past the end: not used
-#pragma unroll
-        for (int b = 0; b < 4; ++b) wv[s][c][b] = *reinterpret_cast<const float4 *>(wr[b] + m);
+        load(s, c, m);
 #pragma unroll
         for (int a = 0; a < 4; ++a) xv[s][c][a].load(xr[a] + m);
       }
     };
-    auto use = [&](int s, int m0) {
+    auto add = [&](int s, int m0) {
 #pragma unroll
       for (int c = 0; c < SS_GC; ++c) {
         if (m0 + 256 * c >= d) break;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            const float xe = xv[s][c][a].at(r);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              const float we = r == 0   ? wv[s][c][b].x
-                               : r == 1 ? wv[s][c][b].y
-                               : r == 2 ? wv[s][c][b].z
-                                        : wv[s][c][b].w;
-              acc[4 * a + b] = __builtin_fmaf(xe, we, acc[4 * a + b]);
-            }
-          }
+        use(s, c);
       }
     };
     fetch(0, 0);
     for (int m0 = 0; m0 < d; m0 += 2 * SS_GC * 256) {
       fetch(1, m0 + SS_GC * 256);
       __builtin_amdgcn_sched_barrier(0);
-      use(0, m0);
+      add(0, m0);
       __builtin_amdgcn_sched_barrier(0);
       if (m0 + 2 * SS_GC * 256 < d) fetch(0, m0 + 2 * SS_GC * 256);
       __builtin_amdgcn_sched_barrier(0);
-      if (m0 + SS_GC * 256 < d) use(1, m0 + SS_GC * 256);
+      if (m0 + SS_GC * 256 < d) add(1, m0 + SS_GC * 256);
     }
+  };
+  if (extra) {   // rows: 0 x itself, 1 G
+    stream(
+        [&](int s, int c, int m) {
+          wv[s][c][0] = G ? *reinterpret_cast<const float4 *>(wr[0] + m) : float4{0.f, 0.f, 0.f, 0.f};
+        },
+        [&](int s, int c) {
+          const float gv[4] = {wv[s][c][0].x, wv[s][c][0].y, wv[s][c][0].z, wv[s][c][0].w};
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float xe = xv[s][c][a].at(r);
+              acc[4 * a] = __builtin_fmaf(xe, xe, acc[4 * a]);
+              acc[4 * a + 1] = __builtin_fmaf(xe, gv[r], acc[4 * a + 1]);
+            }
+        });
+  } else {
+    stream(
+        [&](int s, int c, int m) {
+#pragma unroll
+          for (int b = 0; b < 4; ++b) wv[s][c][b] = *reinterpret_cast<const float4 *>(wr[b] + m);
+        },
+        [&](int s, int c) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              const float xe = xv[s][c][a].at(r);
+#pragma unroll
+              for (int b = 0; b < 4; ++b) {
+                const float we = r == 0   ? wv[s][c][b].x
+                                 : r == 1 ? wv[s][c][b].y
+                                 : r == 2 ? wv[s][c][b].z
+                                          : wv[s][c][b].w;
+                acc[4 * a + b] = __builtin_fmaf(xe, we, acc[4 * a + b]);
+              }
+            }
+        });
   }
   const float v = tree16(acc);   // dot i of (token i / 4, row i % 4) in lanes 4 i ..
   const int i = lane >> 2, t = t0 + (i >> 2), b = i & 3, r = 4 * rg + b;

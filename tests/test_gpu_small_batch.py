@@ -87,7 +87,7 @@ def test_fp32_rows(gu, B, d, I):  # noqa: F811
 
 @pytest.mark.parametrize("B", [1, 4, 5, 16, 17, 63, 64, 65])
 @pytest.mark.parametrize("d,E,bf16,sg", [(256, 3, True, 1), (768, 37, False, 0), (1024, 256, True, 0),
-                                         (2304, 8, True, 1)])
+                                         (1280, 6, True, 1), (2304, 8, True, 1)])
 def test_small_scores(gu, B, d, E, bf16, sg):  # noqa: F811
     _small_scores(gu, B, d, E, bf16, sg)
 
