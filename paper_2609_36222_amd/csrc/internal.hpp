@@ -168,12 +168,25 @@ __host__ __device__ inline unsigned ffn_dn_grid(int n_cu, int kind) {
   return (unsigned)(wpe / 2) * ffn_cu_grid(n_cu);
 }
 
-// rows: n_router of Wr (logits, + beta), then the vector G when given (gdot)
-// scores_small batches may also take the predictor's rows A [n_router]: the
-// dot products of every expert (q [B][n_router]) and ||x||^2 (ss [B]); where
-// the line lies: k_scores_small
+// Few dot products: k_scores_small, which may also take the predictor's rows.
+// With the predictor the line is B <= 64 or B E <= 64 * 128 (its comment in
+// scores.hip has both sides).
 constexpr int SC_SMALL_B = 64, SC_SMALL_DOTS = 64 * 128;
 inline bool scores_small(int B, int E) { return B <= SC_SMALL_B || B * E <= SC_SMALL_DOTS; }
+// Without the predictor (base_route, the other rules, a gate alone with E = 0)
+// the tiles win where a wavefront's ring has nothing to hide, d <= 512 from a
+// whole token group on, and past 128 rows (base_route, us, tiled against small:
+// E = 64, B = 16 d = 256 5.4 and 5.7, d = 1024 6.5 and 6.2, d = 4096 12.2 and
+// 9.6; E = 64, B = 8, d = 512 5.8 and 5.2; E = 160, B = 32 d = 512 8.9 and 9.8, d =
+// 2048 12.4 and 12.3; E = 256, B = 8 d = 256 8.0 and 8.6, d = 2048 12.4 and 10.5;
+// a gate alone, the staged call, B = 300 d = 256 26.3 and 27.3, d = 4096 65.0 and
+// 62.6).
+inline bool scores_small_router(int B, int E, int d) {
+  return scores_small(B, E) && (E <= 128 ? B < TOK_GROUP || d > 512 : B < TOK_GROUP && d > 512);
+}
+// rows: n_router of Wr (logits, + beta), then the vector G when given (gdot);
+// scores_small launches may also take the predictor's rows A [n_router]: the
+// dot products of every expert (q [B][n_router]) and ||x||^2 (ss [B])
 hipError_t launch_scores(bool bf16, const void *x, int B, int d, const float *Wr,
                          const float *beta, int n_router, const float *G, float *logits,
                          float *gdot, hipStream_t st, const float *A = nullptr,

@@ -99,6 +99,14 @@ def test_small_scores_of_many_tokens(gu, B, E):  # noqa: F811
     _small_scores(gu, B, 512, E, True, 1)
 
 
+@pytest.mark.parametrize("B,d,E", [(8, 256, 129), (8, 768, 129), (15, 512, 128), (16, 512, 128),
+                                   (16, 768, 128), (16, 768, 129)])
+def test_scores_lines(gu, B, d, E):  # noqa: F811
+    """Either side of the lines between the scoring kernels, with the
+    predictor's rows in the same launch and without; a gate alone."""
+    _small_scores(gu, B, d, E, True, 1)
+
+
 def _small_scores(gu, B, d, E, bf16, sg):  # noqa: F811
     """Router, predictor and extra rows in one launch: token and row
     remainders, chunks of the contraction that do not fill a pass."""
