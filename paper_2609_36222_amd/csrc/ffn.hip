@@ -797,13 +797,19 @@ void k_down_split(int d, int I, int E, int slots, int budget, int nrec,
 
 // fp32 experts (small layers): one wavefront per (kept slot, two weight rows:
 // an output's gate and up row, or two rows of W_d).  Lane l takes the elements
-// 4 l .. 4 l + 3 of every 256 (16-byte loads) against eight token rows at a
-// time, and the 16 dot products are summed across the lanes together
+// 4 l .. 4 l + 3 of every 256 (16-byte loads) against TB token rows at a
+// time, and the dot products are summed across the lanes together
 // (tree16).  These launches are latency: the slot's plan entries are
 // requested together, the weights before the token list has arrived.  (One
 // token after another with a six-step butterfly each: 9.4 and 15.2 us for
 // gate/up and down at d = 256, I = 512, six experts, B = 8; now 5.2 and 4.0;
-// at B = 64, 49.6 and 105.9 us, now 10.8 and 12.5.)
+// at B = 64, 49.6 and 105.9 us, now 10.8 and 12.5.)  TB is eight, or for the
+// smallest batches 1, 2 or 4: with eight always, B = 1 and 2 paid for the loads
+// and FMAs of tokens that are not there (the FFN and its plan, 4 of 32 experts
+// kept by a batch of one, d = 2048, I = 4096: one token after another 541 us,
+// eight rows 609, one row with four loads ahead 310; d = 256, I = 512: 15.7,
+// 20.6 and 15.0).  Choosing TB by the slot's own tokens in the kernel put the
+// weights' request behind the token list: 5 to 9% slower at B = 32.
 struct F32Slot {
   int u, p0, n;
 };
@@ -821,34 +827,40 @@ __device__ __forceinline__ F32Slot f32_slot(int E, const int32_t *__restrict__ s
   return r;
 }
 constexpr int F32_WAVES = 4;   // wavefronts per workgroup
-constexpr int F32_TB = 8;      // token rows at a time
 
-// Lane 4 i .. 4 i + 3: row i / 8 (r0, r1) times token row i % 8 (tok[]), rows
-// of len elements.
-__device__ __forceinline__ float dots_2x8(const float *__restrict__ r0, const float *__restrict__ r1,
-                                          const float *const (&tok)[F32_TB], int len) {
+// Lanes 4 i .. 4 i + 3: row r0 times token row i % TB (tok[]), lanes 32 on: row
+// r1; rows of len elements.  Each sum is the same whatever TB.
+template <int TB>
+__device__ __forceinline__ float dots_2xn(const float *__restrict__ r0, const float *__restrict__ r1,
+                                          const float *const (&tok)[TB], int len) {
+  static_assert(TB <= 8, "sixteen sums");
   const int lane = lane_id();
   float v[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) v[i] = 0.0f;
-#pragma unroll 2
+#pragma unroll TB < 4 ? 4 : 2
   for (int k = 4 * lane; k < len; k += 4 * WAVE) {
-    float a[4], b[4], t[F32_TB][4];
+    float a[4], b[4], t[TB][4];
     load4(r0 + k, a);
     load4(r1 + k, b);
 #pragma unroll
-    for (int j = 0; j < F32_TB; ++j) load4(tok[j] + k, t[j]);
+    for (int j = 0; j < TB; ++j) load4(tok[j] + k, t[j]);
 #pragma unroll
-    for (int j = 0; j < F32_TB; ++j)
+    for (int j = 0; j < TB; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         v[j] = __builtin_fmaf(t[j][r], a[r], v[j]);
-        v[F32_TB + j] = __builtin_fmaf(t[j][r], b[r], v[F32_TB + j]);
+        v[8 + j] = __builtin_fmaf(t[j][r], b[r], v[8 + j]);
       }
+  }
+  if constexpr (TB == 1) {
+    const float s0 = wave_tree_sum(v[0]), s1 = wave_tree_sum(v[8]);
+    return lane < 32 ? s0 : s1;
   }
   return tree16(v);
 }
 
+template <int TB>
 __global__ __launch_bounds__(F32_WAVES * WAVE)
 void k_gateup_f32(const float *__restrict__ x, int d, int I, int E,
                   const float *__restrict__ w13,
@@ -860,18 +872,19 @@ void k_gateup_f32(const float *__restrict__ x, int d, int I, int E,
   const int i = blockIdx.y * F32_WAVES + wave_id_u(), lane = lane_id();
   if (i >= I) return;
   const float *wg = w13 + ((size_t)sl.u * 2 * I + i) * d;
-  for (int c = 0; c < sl.n; c += F32_TB) {
-    const float *tok[F32_TB];
+  for (int c = 0; c < sl.n; c += TB) {
+    const float *tok[TB];
 #pragma unroll
-    for (int j = 0; j < F32_TB; ++j)
+    for (int j = 0; j < TB; ++j)
       tok[j] = x + (size_t)pair_tok[sl.p0 + min(c + j, sl.n - 1)] * d;
-    const float g = dots_2x8(wg, wg + (size_t)I * d, tok, d);
+    const float g = dots_2xn<TB>(wg, wg + (size_t)I * d, tok, d);
     const float u = xor_lane<32>(g);   // lanes 32 ..: the up row's
-    const int t = c + (lane >> 2);
-    if (lane < 32 && (lane & 3) == 0 && t < sl.n) H[(size_t)(sl.p0 + t) * I + i] = silu(g) * u;
+    const int j = lane >> 2, t = c + j;
+    if (j < TB && (lane & 3) == 0 && t < sl.n) H[(size_t)(sl.p0 + t) * I + i] = silu(g) * u;
   }
 }
 
+template <int TB>
 __global__ __launch_bounds__(F32_WAVES * WAVE)
 void k_down_f32(int d, int I, int E, const float *__restrict__ w2,
                 const int32_t *__restrict__ sel_ids,
@@ -883,14 +896,14 @@ void k_down_f32(int d, int I, int E, const float *__restrict__ w2,
   const int r = 2 * (blockIdx.y * F32_WAVES + wave_id_u()), lane = lane_id();
   if (r >= d) return;
   const float *wd = w2 + ((size_t)sl.u * d + r) * I;
-  for (int c = 0; c < sl.n; c += F32_TB) {
-    const float *tok[F32_TB];
+  for (int c = 0; c < sl.n; c += TB) {
+    const float *tok[TB];
 #pragma unroll
-    for (int j = 0; j < F32_TB; ++j) tok[j] = H + (size_t)(sl.p0 + min(c + j, sl.n - 1)) * I;
-    const int t = c + ((lane >> 2) & 7), p = sl.p0 + min(t, sl.n - 1);
+    for (int j = 0; j < TB; ++j) tok[j] = H + (size_t)(sl.p0 + min(c + j, sl.n - 1)) * I;
+    const int j = (lane >> 2) & 7, t = c + j, p = sl.p0 + min(t, sl.n - 1);
     const float gt = pair_gate[p];
-    const float o = dots_2x8(wd, wd + I, tok, I);
-    if ((lane & 3) == 0 && t < sl.n) pairbuf[(size_t)p * d + r + (lane >> 5)] = gt * o;
+    const float o = dots_2xn<TB>(wd, wd + I, tok, I);
+    if (j < TB && (lane & 3) == 0 && t < sl.n) pairbuf[(size_t)p * d + r + (lane >> 5)] = gt * o;
   }
 }
 
@@ -938,6 +951,10 @@ void k_combine(int B, int d, int kc, const int32_t *__restrict__ pair_of,
   }
 }
 
+// token rows at a time: no more than the batch has (a slot has more only where
+// routes repeat an expert)
+#define BASE_F32(K, B) (B <= 1 ? K<1> : B <= 2 ? K<2> : B <= 4 ? K<4> : K<8>)
+
 hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
                          int I, int E, int K, int budget, int slots, int ns, const void *w13,
                          const void *w13s, const int32_t *sel_ids, const int32_t *n_sel,
@@ -960,7 +977,8 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
              dim3(FFN_WAVES * WAVE), 0, st, d, I, E, ns, (const uint16_t *)w13,
              (const uint16_t *)w13s, hdr, units, (const uint16_t *)x, B, tokoff, (uint16_t *)H);
   } else {
-    launch_k(k_gateup_f32, dim3(budget, (I + F32_WAVES - 1) / F32_WAVES),
+    const auto kern = BASE_F32(k_gateup_f32, B);
+    launch_k(kern, dim3(budget, (I + F32_WAVES - 1) / F32_WAVES),
                        dim3(F32_WAVES * WAVE), 0, st, (const float *)x, d, I,
                        E, (const float *)w13, sel_ids, n_sel, offsets, pair_tok,
                        (float *)H);
@@ -996,7 +1014,8 @@ hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K
              (const uint16_t *)w2,
              (const uint16_t *)w2s, hdr, units, pair_gate, (const uint16_t *)H, pairbuf);
   } else {
-    launch_k(k_down_f32, dim3(budget, (d + 2 * F32_WAVES - 1) / (2 * F32_WAVES)),
+    const auto kern = BASE_F32(k_down_f32, B);
+    launch_k(kern, dim3(budget, (d + 2 * F32_WAVES - 1) / (2 * F32_WAVES)),
                        dim3(F32_WAVES * WAVE), 0, st, d, I, E,
                        (const float *)w2, sel_ids, n_sel, offsets, pair_gate,
                        (const float *)H, pairbuf);

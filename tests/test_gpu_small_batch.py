@@ -33,7 +33,7 @@ def _forward(gu, inp, logits, ids, sel, n_sel, slot, budget, flags):  # noqa: F8
     offsets, pair_tok, pair_gate, pair_of = method.compact(ex, n_ex, slot, gates, budget)
     y_ref = method.moe_restricted64(inp["x"], ex, n_ex, gates,
                                     method.Experts(inp["w13"], inp["w2"], sh.bf16))
-    for packed in (False, True):
+    for packed in (False, True) if sh.bf16 else (False,):
         gl = gu.GpuLayer(inp, packed=packed)
         ws, y = gl.workspace(B, budget), gl.y_like(B)
 
@@ -77,12 +77,26 @@ def test_kept_set_beyond_the_routes(gu):  # noqa: F811
     _forward(gu, inp, logits, ids, sel, 30, slot, 30, 0)
 
 
-@pytest.mark.parametrize("B", [1, 8, 9, 33])
-@pytest.mark.parametrize("d,I", [(256, 64), (768, 320)])
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 8, 9, 33])
+@pytest.mark.parametrize("d,I", [(256, 64), (768, 320), (1280, 1088)])
 def test_fp32_rows(gu, B, d, I):  # noqa: F811
-    """fp32 layers: token batches of eight and their remainders, a row of I
-    shorter than a wavefront's pass and one with a remainder."""
+    """fp32 layers: token batches of 1, 2, 4 and 8 and their remainders, a row of
+    I shorter than a wavefront's pass and ones with a remainder."""
     run_case(gu, W.custom_layer(d, 6, 3, I, B, bf16=False, seed=80 + B), 4, flags=2)
+
+
+@pytest.mark.parametrize("B", [1, 2, 4])
+def test_fp32_slot_of_several_passes(gu, B):  # noqa: F811
+    """Routes that name one expert three times (drop): a slot then holds more
+    pairs than the batch has tokens."""
+    inp = W.custom_layer(512, 12, 4, 128, B, bf16=False, seed=43)
+    logits, ids, _ = carith.route(inp["x"], inp["w_router"], inp["b_router"], 4, 1)
+    ids = np.full_like(ids, 3)
+    ids[:, 1] = 7
+    slot = np.full(12, -1, np.int32)
+    slot[[3, 7]] = [1, 0]
+    offsets = _forward(gu, inp, logits, ids, np.array([7, 3]), 2, slot, 2, 2)
+    assert offsets[2] - offsets[1] == 3 * B
 
 
 @pytest.mark.parametrize("B", [1, 4, 5, 16, 17, 63, 64, 65])
