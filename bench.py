@@ -50,15 +50,6 @@ METRIC = ("MoE decode-step latency (µs) + HBM GB/s vs peak at batch "
           "64/256, budget B_e")
 DOMINANT = "ffn_gateup"
 GRAPH_STEPS = 16   # at most this many decode steps in one graph (loop-form timing)
-
-
-def empty_stages(B, I):
-    """Stages base_decode_layer runs inside another stage's kernel (for a
-    small batch the compaction too)."""
-    small = B <= (32 if I > 2048 else 64)
-    return ("backfill", "gather") + (("compact",) if small else ())
-
-
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 SHAPE_LABEL = {"tiny": "tiny fp32", "olmoe": "OLMoE-shaped", "qwen3_b64": "Qwen3-30B-A3B-shaped",
                "qwen3_b256": "Qwen3-30B-A3B-shaped", "mixtral": "Mixtral-shaped",
@@ -483,7 +474,8 @@ def bench_stack(args, shape, np, torch, W, bd):
     stage_us = np.array([[elapsed_ms(hip, evs[layer][2 * s], evs[layer][2 * s + 1]) * 1e3
                           for s in range(bd.N_STAGES)] for layer in range(L)])
     stage_sum = {bd.STAGES[s]: round(float(stage_us[:, s].sum()), 1)
-                 for s in range(bd.N_STAGES) if bd.STAGES[s] not in empty_stages(B, shape.I)}
+                 for s in range(bd.N_STAGES)
+                 if bd.STAGES[s] in bd.layer_stages(layers[0][1], B, budget)}
     gu_bytes = budget * 2 * shape.I * shape.d * 2
     gu_us = float(stage_us[:, bd.STAGES.index("ffn_gateup")].mean())
     ffn_us = float(stage_us[:, bd.STAGES.index("ffn_gateup")].sum()
@@ -723,8 +715,8 @@ def main():
     # base_decode_layer backfills (and, for a small batch, compacts) inside the
     # selection kernel, and the FFN gathers its own tokens: those stages launch
     # nothing, and their back-to-back event pairs are left out
-    empty = empty_stages(B, shape.I)
-    timed_stages = [s for s in range(bd.N_STAGES) if bd.STAGES[s] not in empty]
+    launched = bd.layer_stages(layers[0][1], B, budget)
+    timed_stages = [s for s in range(bd.N_STAGES) if bd.STAGES[s] in launched]
     stage_mean = {bd.STAGES[s]: round(float(stage_us[:, s].mean()), 2) for s in timed_stages}
     stage_pct = {bd.STAGES[s]: pct(stage_us[:, s]) for s in timed_stages}
 

@@ -364,8 +364,8 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
  * base_select stage 2, base_moe_forward 3 to 8 (base_predict_cost runs the
  * tail kernel in its cost mode, untimed); base_decode_layer runs all of
  * them except that one
- * kernel makes the selection and the backfill (and, for batches of at most 64,
- * or 32 when I > 2048, the compaction): stage 2 times it and stage 3 (and 4)
+ * kernel makes the selection and the backfill (and, for small batches, the
+ * compaction; base_layer_stages): stage 2 times it and stage 3 (and 4)
  * records its pair back to back.  The setting belongs
  * to the calling host thread; the caller keeps the events alive while it
  * is set.  Calls on a stream that is being captured ignore it (no event is
@@ -373,6 +373,13 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
  * Returns BASE_ERR_SHAPE if n_events != 2 * BASE_N_STAGES. */
 #define BASE_N_STAGES 9
 base_status base_set_stage_events(void *const *events, int32_t n_events);
+
+/* The stages for which base_decode_layer launches a kernel of their own for
+ * this layer, batch and budget: bit i of *stages (host memory) is set for
+ * stage i, clear where another stage's kernel does its work.  Host only; the
+ * layer's pointers are not looked at. */
+base_status base_layer_stages(const base_layer *L, int32_t B, int32_t budget,
+                              int32_t *stages);
 
 /* Static description of a status code. */
 const char *base_status_string(int32_t status);

@@ -23,7 +23,8 @@ SCORE_BASE, SCORE_TOP1, SCORE_WEIGHT, SCORE_WEIGHT_SQ, SCORE_STATIC = 0, 1, 2, 3
 EXPORTS = ("base_workspace_bytes", "base_route", "base_predict_cost",
            "base_select", "base_moe_forward", "base_decode_layer",
            "base_decode_layer_noalloc",
-           "base_pack_experts", "base_set_stage_events", "base_status_string",
+           "base_pack_experts", "base_set_stage_events", "base_layer_stages",
+           "base_status_string",
            "base_calib_stats_bytes", "base_calib_ws_bytes", "base_calib_reset",
            "base_calib_accumulate")
 CALIB_LIB_PATH = os.path.join(HERE, "_lib", "libbase_calib.so")
@@ -104,6 +105,9 @@ def load(path: str = LIB_PATH):
     L.base_pack_experts.argtypes = [ctypes.POINTER(base_layer), _vp, _vp, _vp]
     L.base_set_stage_events.restype = _i32
     L.base_set_stage_events.argtypes = [ctypes.POINTER(ctypes.c_void_p), _i32]
+    L.base_layer_stages.restype = _i32
+    L.base_layer_stages.argtypes = [ctypes.POINTER(base_layer), _i32, _i32,
+                                    ctypes.POINTER(_i32)]
     L.base_status_string.restype = ctypes.c_char_p
     L.base_status_string.argtypes = [_i32]
     L.base_calib_stats_bytes.restype = ctypes.c_size_t
@@ -298,6 +302,13 @@ def base_set_stage_events(events):
     arr = (ctypes.c_void_p * len(events))(*events)
     _check(load().base_set_stage_events(arr, len(events)))
     return arr   # keep alive while timing is on
+
+
+def layer_stages(desc, B, budget):
+    """Names of the stages base_decode_layer launches a kernel for."""
+    m = _i32()
+    _check(load().base_layer_stages(ctypes.byref(desc), B, budget, ctypes.byref(m)))
+    return tuple(s for i, s in enumerate(STAGES) if m.value >> i & 1)
 
 
 # App. A: the ridge's lambdas, 25 values log-spaced over [1e-4, 1e2]

@@ -605,6 +605,19 @@ base_status base_pack_experts(const base_layer *L, void *w13_packed,
   return BASE_OK;
 }
 
+base_status base_layer_stages(const base_layer *L, int32_t B, int32_t budget,
+                              int32_t *stages) {
+  BASE_TRY(check_layer(L, B, false, false, false));
+  if (budget < 1) return BASE_ERR_BUDGET;
+  if (!stages) return BASE_ERR_NULL;
+  int32_t m = (1 << BASE_N_STAGES) - 1;
+  m &= ~(1 << 3);   // the backfill: with the selection
+  if (ffn_split(B, L->I)) m &= ~(1 << 4);   // so is a small batch's compaction
+  m &= ~(1 << 5);   // gate/up gathers its own tokens
+  *stages = m;
+  return BASE_OK;
+}
+
 base_status base_set_stage_events(void *const *events, int32_t n_events) {
   if (!events) {
     g_stage_events = nullptr;

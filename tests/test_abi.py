@@ -304,3 +304,26 @@ def test_noalloc_validation(lib):
     big = layer(E=256, K=16)
     assert lib.base_workspace_bytes(ctypes.byref(big), 1024, 256) > bd.NOALLOC_SCRATCH_BYTES
     assert na(big, B=1024, budget=256) == WS
+
+
+@pytest.mark.parametrize("B,kw,compacts", [
+    (1, {}, False), (64, {}, False), (65, {}, True), (256, {}, True),
+    (32, dict(I=2112), False), (33, dict(I=2112), True),
+    (64, dict(dtype=0, d=256, I=512), False), (65, dict(dtype=0, d=256, I=512), True)])
+def test_layer_stages(lib, B, kw, compacts):
+    """The stages a layer launches kernels for: the compaction has its own
+    beyond the small batches."""
+    st = bd.layer_stages(layer(**kw), B, 32)
+    assert st == tuple(s for s in bd.STAGES
+                       if s not in ("backfill", "gather") and (compacts or s != "compact"))
+
+
+def test_layer_stages_errors(lib):
+    m = ctypes.c_int32(-7)
+
+    def call(L, B=16, budget=4, p=ctypes.byref(m)):
+        return lib.base_layer_stages(None if L is None else ctypes.byref(L), B, budget, p)
+    assert call(None) == NULL and call(layer(), p=None) == NULL
+    assert call(layer(), B=0) == SHAPE and call(layer(), budget=0) == BUDGET
+    assert call(layer(d=100)) == SHAPE and call(layer(dtype=3)) == DTYPE
+    assert m.value == -7
