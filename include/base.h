@@ -191,8 +191,8 @@ typedef struct base_plan {
 } base_plan;
 
 /* Bytes of workspace base_moe_forward / base_decode_layer need for this
- * layer, batch and budget (0 if the shape is invalid).  The workspace must
- * be 256-byte aligned. */
+ * layer, batch and budget, or any smaller budget (0 if the shape is invalid).
+ * The workspace must be 256-byte aligned. */
 size_t base_workspace_bytes(const base_layer *L, int32_t B, int32_t budget);
 
 /* Router (Sec. 3.1; App. "Custom GPU Kernels": the routing stage provides
@@ -274,7 +274,7 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
  * a static device array, kept until the process ends).  The call allocates
  * nothing and calls no allocating routine; the caller still owns x, y and
  * residual.  Results are bit for bit those of base_decode_layer.
- *   Limit: a layer, batch and budget whose base_workspace_bytes exceeds
+ *   Limit: a layer, batch and budget whose workspace exceeds
  *          BASE_NOALLOC_SCRATCH_BYTES returns BASE_ERR_WORKSPACE (64 MiB
  *          covers, e.g., d = 2048, E = 128, K = 8, I = 768 at B = 256 with
  *          any budget up to E).

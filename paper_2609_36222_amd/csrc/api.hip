@@ -90,8 +90,10 @@ base_status check_ptr(const void *p, size_t a) {
     if ((expr) != hipSuccess) return BASE_ERR_HIP; \
   } while (0)
 
-// Workspace layout: every array starts on a 256-byte boundary.
+// Workspace layout: every array starts on a 256-byte boundary.  split: the FFN
+// takes its split kernels (bf16).
 struct Layout {
+  bool split;
   size_t logits, gdot, topk_ids, topk_w, cost, scores, counts, sel_ids, n_sel,
       slot_of, exec_ids, exec_gates, offsets, pair_tok, pair_gate, pair_of, order, ex,
       den, hdr, units_gu, units_dn, tokoff, sprec, H, pairbuf, total;
@@ -99,8 +101,9 @@ struct Layout {
 
 size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-Layout layout(const base_layer *L, int32_t B, int32_t bc) {
+Layout layout(const base_layer *L, int32_t B, int32_t bc, bool split) {
   Layout o;
+  o.split = split;
   size_t at = 0;
   auto take = [&](size_t bytes) {
     size_t here = at;
@@ -134,7 +137,7 @@ Layout layout(const base_layer *L, int32_t B, int32_t bc) {
   // the FFN's part tables and their header (bf16)
   const bool bf = L->dtype == BASE_BF16;
   // (one header per die; every die's run of units written on that die)
-  const bool units = bf && !ffn_split(B, L->I), split = bf && ffn_split(B, L->I);
+  const bool units = bf && !split;
   const size_t ug = units ? (size_t)ffn_units_bound_gu(B, L->K, bc, ns, L->I) : 0;
   const size_t ud = units ? (size_t)ffn_units_bound_dn(B, L->K, bc, ns, L->d) : 0;
   o.hdr = take(units ? N_XCD * sizeof(FfnHdr) : 0);
@@ -157,6 +160,30 @@ Layout layout(const base_layer *L, int32_t B, int32_t bc) {
   static_assert(MAX_E <= 256, "q in the pair rows' buffer");
   o.total = at;
   return o;
+}
+
+// The layout of a call, with its choice of FFN kernels.  A small batch that
+// would take the unit kernels keeps the split ones where only their smaller
+// workspace fits the fixed scratch, so that base_decode_layer_noalloc, whose
+// results are base_decode_layer's, takes it too.
+Layout layout(const base_layer *L, int32_t B, int32_t bc) {
+  const bool bf = L->dtype == BASE_BF16;
+  const Layout s = layout(L, B, bc, bf && ffn_small(B, L->I));
+  if (!s.split || ffn_split(B, L->K, L->d, L->I, bc, L->n_shared)) return s;
+  const Layout u = layout(L, B, bc, false);
+  return u.total > BASE_NOALLOC_SCRATCH_BYTES && s.total <= BASE_NOALLOC_SCRATCH_BYTES ? s : u;
+}
+
+// base_workspace_bytes: a workspace sized for one budget holds every smaller one,
+// also where only those take the unit kernels and their tables.
+size_t workspace_bytes(const base_layer *L, int32_t B, int32_t bc) {
+  const Layout o = layout(L, B, bc);
+  if (!o.split) return o.total;
+  for (int32_t b = bc - 1; b >= 1; --b) {
+    const Layout u = layout(L, B, b);
+    if (!u.split) return std::max(o.total, u.total);
+  }
+  return o.total;
 }
 
 // kernel timing (base_set_stage_events), per host thread
@@ -255,14 +282,14 @@ base_status run_forward(const base_layer *L, const void *x, int32_t B,
   FfnHdr *hdr = at<FfnHdr>(ws, o.hdr);
   FfnUnit *units_gu = at<FfnUnit>(ws, o.units_gu), *units_dn = at<FfnUnit>(ws, o.units_dn);
   uint32_t *tokoff = at<uint32_t>(ws, o.tokoff);
-  SpRec *rec = bf16 && ffn_split(B, L->I) ? at<SpRec>(ws, o.sprec) : nullptr;
+  SpRec *rec = o.split ? at<SpRec>(ws, o.sprec) : nullptr;
   int32_t *sptok = at<int32_t>(ws, o.pairbuf);
   // the same launch lists the FFN's parts and gate/up's token rows (bf16)
   if (!planned)
     HIP_TRY(launch_compact(B, L->K, L->E, bc, ns, exec_ids, exec_gates, slot_of, n_sel,
                            shared_gate(L) ? at<float>(ws, o.gdot) : nullptr, offsets,
-                           pair_tok, pair_gate, pair_of, sel_ids, bf16 && !ffn_split(B, L->I), L->d, L->I, tokoff,
-                           hdr, units_gu, units_dn, rec, sptok, n_cu, st));
+                           pair_tok, pair_gate, pair_of, sel_ids, bf16 && !o.split, L->d, L->I, tokoff, hdr,
+                           units_gu, units_dn, rec, sptok, n_cu, st));
   stage_end(st);
   stage(5, st);   // no launch of its own: gate/up gathers its tokens itself
   stage_end(st);
@@ -285,6 +312,12 @@ base_status run_forward(const base_layer *L, const void *x, int32_t B,
                          residual, y, st));
   stage_end(st);
   return BASE_OK;
+}
+
+// the fused layer's plan in one launch: the split kernels' records (bf16), or
+// nothing but the plan (fp32)
+bool one_plan(const base_layer *L, int32_t B, const Layout &o) {
+  return L->dtype == BASE_BF16 ? o.split : ffn_small(B, L->I);
 }
 
 void fill_plan(base_plan *P, void *ws, const Layout &o, bool full) {
@@ -324,7 +357,7 @@ extern "C" {
 
 size_t base_workspace_bytes(const base_layer *L, int32_t B, int32_t budget) {
   if (check_layer(L, B, false, false, false) != BASE_OK || budget < 1) return 0;
-  return layout(L, B, budget < L->E ? budget : L->E).total;
+  return workspace_bytes(L, B, budget < L->E ? budget : L->E);
 }
 
 base_status base_route(const base_layer *L, const void *x, int32_t B,
@@ -457,15 +490,15 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
                       L->pred_b, ids, w, cost, 3, L->score_rule, st, order, ex, den, qd, ss));
   stage_end(st);
   stage(2, st);   // selection and backfill in one launch
-  const bool split = ffn_split(B, L->I);   // ... and, for a small batch, the compaction
-  if (split)
+  const bool joined = one_plan(L, B, o);   // ... and, for a small batch, the compaction
+  if (joined)
     HIP_TRY(launch_plan_split(
         B, L->K, L->E, bc, L->n_shared, L->score_rule == BASE_SCORE_TOP1, flags, ids, cost, order,
         ex, den, shared_gate(L) ? at<float>(ws, o.gdot) : nullptr, at<float>(ws, o.scores),
         at<int32_t>(ws, o.counts), sel, nsel, slot, at<int32_t>(ws, o.exec_ids),
         at<float>(ws, o.exec_gates), at<int32_t>(ws, o.offsets), at<int32_t>(ws, o.pair_tok),
         at<float>(ws, o.pair_gate), at<int32_t>(ws, o.pair_of),
-        bf16 ? at<SpRec>(ws, o.sprec) : nullptr, at<int32_t>(ws, o.pairbuf), st));
+        o.split ? at<SpRec>(ws, o.sprec) : nullptr, at<int32_t>(ws, o.pairbuf), st));
   else
     HIP_TRY(launch_select_backfill(B, L->K, L->E, ids, cost, bc,
                                    L->score_rule == BASE_SCORE_TOP1, flags, order, ex, den,
@@ -474,7 +507,7 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
                                    device_cus(), st));
   stage_end(st);
   BASE_TRY(run_forward(L, x, B, logits, ids, sel, nsel, slot, bc, flags,
-                       residual, y, ws, o, st, true, split));
+                       residual, y, ws, o, st, true, joined));
   fill_plan(plan_out, ws, o, true);
   return BASE_OK;
 }
@@ -564,12 +597,12 @@ base_status base_calib_accumulate(const base_layer *L, const void *z, int32_t B,
   const int n_cu = device_cus();
   FfnHdr *hdr = at<FfnHdr>(ws, o.hdr);
   FfnUnit *units_gu = at<FfnUnit>(ws, o.units_gu), *units_dn = at<FfnUnit>(ws, o.units_dn);
-  SpRec *rec = bf16 && ffn_split(B, C.I) ? at<SpRec>(ws, o.sprec) : nullptr;
+  SpRec *rec = o.split ? at<SpRec>(ws, o.sprec) : nullptr;
   int32_t *sptok = at<int32_t>(ws, o.pairbuf);
   HIP_TRY(launch_compact(B, C.K, C.E, bc, 0, at<int32_t>(ws, o.exec_ids),
                          at<float>(ws, o.exec_gates), slot, nsel, nullptr, offsets, pair_tok,
                          at<float>(ws, o.pair_gate), at<int32_t>(ws, o.pair_of), sel,
-                         bf16 && !ffn_split(B, C.I), C.d, C.I, at<uint32_t>(ws, o.tokoff), hdr, units_gu, units_dn,
+                         bf16 && !o.split, C.d, C.I, at<uint32_t>(ws, o.tokoff), hdr, units_gu, units_dn,
                          rec, sptok, n_cu, st));
   const bool packed = C.w_layout == BASE_W_PACKED;
   HIP_TRY(launch_gateup(bf16, packed, z, B, C.d, C.I, C.E, C.K, bc, std::min(bc, B * C.K), 0, C.w13, nullptr, sel,
@@ -612,7 +645,8 @@ base_status base_layer_stages(const base_layer *L, int32_t B, int32_t budget,
   if (!stages) return BASE_ERR_NULL;
   int32_t m = (1 << BASE_N_STAGES) - 1;
   m &= ~(1 << 3);   // the backfill: with the selection
-  if (ffn_split(B, L->I)) m &= ~(1 << 4);   // so is a small batch's compaction
+  if (one_plan(L, B, layout(L, B, budget < L->E ? budget : L->E)))
+    m &= ~(1 << 4);   // so is a small batch's compaction
   m &= ~(1 << 5);   // gate/up gathers its own tokens
   *stages = m;
   return BASE_OK;

@@ -491,7 +491,7 @@ void k_down_bf16(int d, int I, int E, int ns, const uint16_t *__restrict__ w2r,
 static_assert(FFN_DN_PT == 8, "down tile-count cases");
 
 // ----------------------------------------------------------------------------
-// Small batches (ffn_split): every slot's pairs fit four 16-pair tiles, so a
+// Small batches (ffn_split; bf16): every slot's pairs fit four 16-pair tiles, so a
 // row group's weights meet few tokens and the launch is a weight stream.
 // One workgroup per (slot, row group); its SP_WAVES wavefronts split the
 // contraction (wavefront w: the w-th contiguous share of the k-steps), each
@@ -962,7 +962,7 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
                          const FfnHdr *hdr, const FfnUnit *units, int n_cu,
                          const uint32_t *tokoff, const SpRec *rec, const int32_t *sptok, void *H,
                          hipStream_t st) {
-  if (bf16 && ffn_split(B, I)) {
+  if (rec) {
     const dim3 grid(I / 16 / SPG_RT, slots + ns);
 #define BASE_GS(N, P) k_gateup_split<N, SPG_RT, P>
     const auto kern = B <= 16   ? (packed ? BASE_GS(1, true) : BASE_GS(1, false))
@@ -992,7 +992,7 @@ hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K
                        const int32_t *n_sel, const int32_t *offsets,
                        const FfnHdr *hdr, const FfnUnit *units, const SpRec *rec, int n_cu,
                        const float *pair_gate, const void *H, float *pairbuf, hipStream_t st) {
-  if (bf16 && ffn_split(B, I)) {
+  if (rec) {
     const dim3 grid(d / 16 / (B <= 16 ? SPD_RT1 : SPD_RT2), slots + ns);
 #define BASE_DS(N, R, P) k_down_split<N, R, P>
     const auto kern = B <= 16   ? (packed ? BASE_DS(1, SPD_RT1, true) : BASE_DS(1, SPD_RT1, false))

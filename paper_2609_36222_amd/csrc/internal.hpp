@@ -104,20 +104,48 @@ constexpr uint32_t FFN_TOK_PAD = 0x80000000u;   // past every x: a buffer load r
 static_assert(FFN_GU_PT <= FFN_WAVES, "one token tile per gate/up wavefront");
 static_assert((size_t)MAX_B * 16384 * 2 < FFN_TOK_PAD, "token row offsets below the pad mark");
 
-// Batches of at most FFN_SPLIT_B tokens (FFN_SPLIT_LONG_B when down's
-// contraction is long) take the FFN's split kernels (see "Small batches" in
-// ffn.hip), which need no unit tables, and the fused layer makes their plan in
-// one launch (k_plan_split).  A slot then holds at most four 16-pair tiles and
-// the FFN is a weight stream.  Measured per layer against the unit kernels and
-// two plan launches (us): Qwen3-shaped, ten kept experts, B = 1 60 -> 38, B = 16
-// 65 -> 45, B = 48 67 -> 54; 32 kept, B = 64 95 -> 87; OLMoE-shaped B = 32 76 ->
-// 63, B = 64 79 -> 71; row-major Qwen1.5-MoE-shaped B = 31 120 -> 103, B = 61
-// 127 -> 115; Mixtral-shaped B = 32 295 -> 268, but at B = 64 295 -> 300 (its
-// gate/up, with 32 pairs a slot, reads as many token bytes as weights).
-// Beyond 64 the token reads exceed the weights'.
+// Small batches, at most FFN_SPLIT_B tokens (FFN_SPLIT_LONG_B when down's
+// contraction is long): the fused layer makes its plan in one launch
+// (k_plan_split) and the bf16 FFN takes its split kernels (see "Small batches"
+// in ffn.hip), which need no unit tables.  A slot then holds at most four
+// 16-pair tiles and the FFN is a weight stream.  Measured per layer against the
+// unit kernels and two plan launches (us): Qwen3-shaped, ten kept experts, B = 1
+// 60 -> 38, B = 16 65 -> 45, B = 48 67 -> 54; 32 kept, B = 64 95 -> 87;
+// OLMoE-shaped B = 32 76 -> 63, B = 64 79 -> 71; row-major Qwen1.5-MoE-shaped B =
+// 31 120 -> 103, B = 61 127 -> 115; Mixtral-shaped B = 32 295 -> 268.  Long
+// contractions between 32 and 64 tokens gain and lose (Mixtral-shaped B = 64 295
+// -> 300; I = 2496 to 5952, d = 1536 to 4096, us: 48 tokens on 2 slots 1.20
+// times faster, 36 on 2 1.27, 60 on 4 0.88, 64 on 4 0.88, 48 tokens on 42 slots
+// 1.02).
 constexpr int FFN_SPLIT_B = 64, FFN_SPLIT_LONG_B = 32;
-__host__ __device__ inline bool ffn_split(int B, int I) {
+__host__ __device__ inline bool ffn_small(int B, int I) {
   return B <= (ffn_dn_long(I) ? FFN_SPLIT_LONG_B : FFN_SPLIT_B);
+}
+// The split kernels read a slot's token rows four times as often as the unit
+// kernels (a workgroup has two row-pair tiles, not eight), so what they lose
+// grows with the pairs past a slot's first 16 and with the expert's size, and
+// what they gain is mostly fixed, the launches' starts and steps.  The line is
+// (pairs - 16 slots) d I = FFN_SPLIT_EXTRA; over 800 packed layers of B <= 64
+// (20 MB to 1.4 GB of kept weights, split against unit kernels, the fused layer
+// and base_moe_forward): every slot full, B = 64, 16 slots of d = 4096, I = 2048
+// 223 and 222 us split, 196 and 173 with units; 10 slots of d = 2048, I = 2048
+// 104 and 86 against 95 and 70; 4 slots of d = 2048, I = 1408 (below the line)
+// 52 and 39 against 61 and 48.  Below the line the split kernels win by 1.2
+// times in the mean, just below it the fused layer by a few per cent, with the
+// plan launch it saves, and base_moe_forward, which saves none, loses up to 1.16
+// times (8 slots of d = 4096, I = 1280, B = 60: 105 and 79 us split, 106 and 67
+// with units); the two have to take the same kernels.  With at most 16 tokens no
+// slot has more than one tile.  Row-major weights would keep the split
+// kernels longer (8 of 217 layers past the line, by up to 1.17 times: the unit
+// kernels read them 64 bytes at a time), but both layouts have to take the same
+// sums.
+constexpr int64_t FFN_SPLIT_EXTRA = 1800000000;
+inline bool ffn_split(int B, int K, int d, int I, int budget, int ns) {
+  if (!ffn_small(B, I)) return false;
+  if (B <= 16) return true;
+  const int kept = budget < B * K ? budget : B * K;
+  const int64_t pairs = (int64_t)B * ((K < kept ? K : kept) + ns);
+  return (pairs - 16 * (kept + ns)) * d * I <= FFN_SPLIT_EXTRA;
 }
 
 // Slot s of a small batch for the split kernels, one copy per die (written by
@@ -231,7 +259,7 @@ hipError_t launch_select_backfill(int B, int K, int E, const int32_t *ids, const
                                   int32_t *counts, int32_t *sel_ids, int32_t *n_sel,
                                   int32_t *slot_of, int32_t *exec_ids, float *exec_gates,
                                   int n_cu, hipStream_t st);
-// selection, backfill and compaction in one launch, for ffn_split batches
+// selection, backfill and compaction in one launch, for ffn_small batches
 // (same results as the three); rec / sptok (bf16 layers, else null): the split
 // kernels' records and token lists
 hipError_t launch_plan_split(int B, int K, int E, int budget, int ns, bool binary, int flags,
@@ -273,7 +301,7 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
                          const int32_t *offsets, const int32_t *pair_tok,
                          const FfnHdr *hdr, const FfnUnit *units, int n_cu,
                          const uint32_t *tokoff, const SpRec *rec, const int32_t *sptok, void *H,
-                         hipStream_t st);
+                         hipStream_t st);   // rec: the split kernels, else the unit kernels
 hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K,
                        int budget, int slots, int ns, const void *w2, const void *w2s,
                        const int32_t *sel_ids,

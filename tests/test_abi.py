@@ -309,7 +309,13 @@ def test_noalloc_validation(lib):
 @pytest.mark.parametrize("B,kw,compacts", [
     (1, {}, False), (64, {}, False), (65, {}, True), (256, {}, True),
     (32, dict(I=2112), False), (33, dict(I=2112), True),
-    (64, dict(dtype=0, d=256, I=512), False), (65, dict(dtype=0, d=256, I=512), True)])
+    (64, dict(dtype=0, d=256, I=512), False), (65, dict(dtype=0, d=256, I=512), True),
+    # full slots of wide experts: (pairs - 16 slots) d I past 1.8e9
+    (64, dict(d=4096, E=32, K=16, I=2048), True), (16, dict(d=4096, E=32, K=16, I=2048), False),
+    (64, dict(d=4096, E=32, K=4, I=2048), False), (64, dict(E=4, K=4, I=1408), False),
+    (48, dict(E=2, K=2, I=2048, n_shared=8, w_layout=1), False),
+    (64, dict(E=2, K=2, I=2048, n_shared=8, w_layout=1), True),
+    (64, dict(dtype=0, d=4096, E=32, K=16, I=2048), False)])
 def test_layer_stages(lib, B, kw, compacts):
     """The stages a layer launches kernels for: the compaction has its own
     beyond the small batches."""
@@ -327,3 +333,20 @@ def test_layer_stages_errors(lib):
     assert call(layer(), B=0) == SHAPE and call(layer(), budget=0) == BUDGET
     assert call(layer(d=100)) == SHAPE and call(layer(dtype=3)) == DTYPE
     assert m.value == -7
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(d=4096, E=32, K=16, I=2048), dict(d=4096, K=4, I=2048),
+                                dict(d=2048, E=8, K=2, I=2048, n_shared=8),
+                                dict(d=1024, E=60, K=12, I=4096), dict(dtype=0, d=256, I=512)])
+def test_workspace_grows_with_batch_and_budget(lib, kw):
+    """A workspace made for the largest batch and budget of a program serves its
+    smaller ones, whichever kernels those take."""
+    L = layer(**kw)
+    rows = [[lib.base_workspace_bytes(ctypes.byref(L), B, b) for b in range(1, L.E + 1)]
+            for B in [*range(1, 140), 255, 256, 1023, 1024]]
+    for r in rows:
+        assert all(0 < x <= y for x, y in zip(r, r[1:]))
+    for r, q in zip(rows, rows[1:]):
+        assert all(x <= y for x, y in zip(r, q))
+    calib = [lib.base_calib_ws_bytes(ctypes.byref(L), B) for B in range(1, 140)]
+    assert all(0 < x <= y for x, y in zip(calib, calib[1:]))

@@ -151,6 +151,19 @@ def test_long_contraction(gu):  # noqa: F811
     run_case(gu, W.custom_layer(2048, 4, 2, 2112, 70, seed=97), 2)
 
 
+def test_full_slots_either_side_of_the_line(gu):  # noqa: F811
+    """Every slot full of pairs: the split kernels, their plan in one launch, up
+    to (pairs - 16 slots) d I = 1.8e9, beyond it the unit kernels; every plan
+    array against the oracle, staged equal to fused and packed to row-major."""
+    from paper_2609_36222_amd import binding as bd
+    inp = W.custom_layer(2048, 12, 12, 1024, 64, seed=44, n_shared=6)
+    for B, compacts in ((60, False), (64, True)):
+        part = dict(inp, x=inp["x"][:B])
+        desc = gu.GpuLayer(part).desc
+        assert ("compact" in bd.layer_stages(desc, B, 12)) == compacts
+        run_case(gu, part, 12)
+
+
 @pytest.mark.parametrize("B", [511, 513, 600])
 def test_selection_workgroups(gu, B):  # noqa: F811
     """Where the fused selection takes more tokens per workgroup."""
