@@ -324,8 +324,10 @@ base_status base_pack_experts(const base_layer *L, void *w13_packed,
  * z_bar = z_t / ||z_t|| (fp64); per expert u the statistics add
  *   n_u, sum y, sum y^2                (fp64),
  *   sum z_bar [d], sum z_bar y [d]     (fp64),
- *   G_u = sum z_bar z_bar^T [d][d]     (fp32 products and sums per batch,
- *                                       on the matrix cores, then one add).
+ *   G_u = sum z_bar z_bar^T [d][d]     (fp32 sums per batch on the matrix
+ *                                       cores, then one add; products of fp32
+ *                                       z_bar, for bf16 layers of the bf16 row
+ *                                       times fp32 z_t / ||z_t||^2).
  * G_u is kept exactly symmetric: each call reads only the blocks on and
  * above the diagonal (128 x 128 blocks) and writes the new values there and,
  * transposed, below; statistics not made by base_calib_reset and this call

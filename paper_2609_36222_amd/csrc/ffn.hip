@@ -9,6 +9,10 @@
 //   per instruction, tokens padded to 16).
 // k_down_bf16 (part, row tiles of d): pairbuf[p][c] = gate_p * (H[p] . W_d[c]).
 // Each unit streams its weight rows once; see "Grouped bf16 FFN" below.
+// k_gateup_split, k_down_split (kept slot, row tiles): the same for small
+//   batches, a workgroup's wavefronts sharing the contraction, H as rows; see
+//   "Small batches" below.
+// k_gateup_f32, k_down_f32 (kept slot, two weight rows): fp32 layers.
 // k_combine: y_t = residual_t + sum_j pairbuf[pair_of[t][j]] in j order
 //   (the K routed ranks, then the shared experts).
 //

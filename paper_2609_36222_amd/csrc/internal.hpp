@@ -114,9 +114,9 @@ static_assert((size_t)MAX_B * 16384 * 2 < FFN_TOK_PAD, "token row offsets below 
 // OLMoE-shaped B = 32 76 -> 63, B = 64 79 -> 71; row-major Qwen1.5-MoE-shaped B =
 // 31 120 -> 103, B = 61 127 -> 115; Mixtral-shaped B = 32 295 -> 268.  Long
 // contractions between 32 and 64 tokens gain and lose (Mixtral-shaped B = 64 295
-// -> 300; I = 2496 to 5952, d = 1536 to 4096, us: 48 tokens on 2 slots 1.20
-// times faster, 36 on 2 1.27, 60 on 4 0.88, 64 on 4 0.88, 48 tokens on 42 slots
-// 1.02).
+// -> 300; the layer split against unit kernels, d = 512 to 4096: 36 and 48 tokens
+// on 2 slots, I = 5504 and 4800, 1.27 and 1.20 times faster, 48 on 42, I = 2112,
+// 1.02, 60 and 64 on 4, I = 4416 and 5952, 0.88).
 constexpr int FFN_SPLIT_B = 64, FFN_SPLIT_LONG_B = 32;
 __host__ __device__ inline bool ffn_small(int B, int I) {
   return B <= (ffn_dn_long(I) ? FFN_SPLIT_LONG_B : FFN_SPLIT_B);
@@ -130,7 +130,7 @@ __host__ __device__ inline bool ffn_small(int B, int I) {
 // and base_moe_forward): every slot full, B = 64, 16 slots of d = 4096, I = 2048
 // 223 and 222 us split, 196 and 173 with units; 10 slots of d = 2048, I = 2048
 // 104 and 86 against 95 and 70; 4 slots of d = 2048, I = 1408 (below the line)
-// 52 and 39 against 61 and 48.  Below the line the split kernels win by 1.2
+// 43 and 35 against 59 and 45.  Below the line the split kernels win by 1.2
 // times in the mean, just below it the fused layer by a few per cent, with the
 // plan launch it saves, and base_moe_forward, which saves none, loses up to 1.16
 // times (8 slots of d = 4096, I = 1280, B = 60: 105 and 79 us split, 106 and 67

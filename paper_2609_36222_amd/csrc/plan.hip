@@ -15,6 +15,7 @@
 //            rank) pairs by kept slot, the token lists of the grouped FFN.
 // k_select_backfill  the first two in one launch (the fused layer): every
 //            workgroup repeats the selection and backfills its own tokens.
+// k_plan_split  all three in one launch (the fused layer's small batches).
 #include <algorithm>
 
 #include "common.hpp"
@@ -118,14 +119,14 @@ __device__ __forceinline__ int select_rank(SelLds &S, int E, int budget, int bin
 // token 64c + j if it routes u, else +0); one thread per (chunk, expert)
 // adds its row by the halving tree, and the chunk sums are added to D_hat_u
 // in ascending chunk order; then the kept set (select_rank).
-__device__ __forceinline__ int select_body(SelLds &S, int B, int K, int E, int budget,
+__device__ __forceinline__ void select_body(SelLds &S, int B, int K, int E, int budget,
                                            int binary, const int (&uk)[MAX_K],
-                                           const float (&ck)[MAX_K], bool out,
+                                           const float (&ck)[MAX_K],
                                            float *__restrict__ scores,
                                            int32_t *__restrict__ counts,
                                            int32_t *__restrict__ sel_ids,
                                            int32_t *__restrict__ n_sel_out,
-                                           int32_t *__restrict__ slot_of, int *slot_lds) {
+                                           int32_t *__restrict__ slot_of) {
   const int tid = threadIdx.x, lane = lane_id();
   for (int u = tid; u < E; u += SEL_THREADS) { S.cnt[u] = 0; S.D[u] = 0.0f; }
   if (tid == 0) S.n_union = 0;
@@ -169,8 +170,7 @@ __device__ __forceinline__ int select_body(SelLds &S, int B, int K, int E, int b
     __syncthreads();
   }
 
-  return select_rank(S, E, budget, binary, out, scores, counts, sel_ids, n_sel_out, slot_of,
-                     slot_lds);
+  select_rank(S, E, budget, binary, true, scores, counts, sel_ids, n_sel_out, slot_of, nullptr);
 }
 
 // The same aggregation for routes that are distinct within a token (the fused
@@ -313,8 +313,7 @@ void k_select(int B, int K, int E, const int32_t *__restrict__ ids,
   int uk[MAX_K];
   float ck[MAX_K];
   load_routes(B, K, ids, cost, S.V, uk, ck);
-  select_body(S, B, K, E, budget, binary, uk, ck, true, scores, counts, sel_ids, n_sel_out,
-              slot_of, nullptr);
+  select_body(S, B, K, E, budget, binary, uk, ck, scores, counts, sel_ids, n_sel_out, slot_of);
 }
 
 constexpr int BF_WAVES = 4;
@@ -469,7 +468,7 @@ void k_backfill(int B, int E, int K, int norm_topk, int flags,
 // Selection and backfill in one launch (the fused layer): every workgroup
 // makes the batch's selection itself (the same fixed-order arithmetic, so
 // the same result everywhere; workgroup 0 writes it out) and then backfills
-// its own SB_TOK tokens, one per wavefront, on the tokens' own die.  The
+// its own 1 << sbl tokens, one per wavefront, on the tokens' own die.  The
 // backfill takes the token's experts in rank order (order, written by
 // k_tail with exp(l - l_max) in rank order, ex, and the router's
 // denominator S, den), requested before the selection: the first
@@ -545,7 +544,7 @@ void k_select_backfill(int B, int K, uint64_t kmul, int E, int sbl, const int32_
   for (int c = 0; c < NCH; ++c) {
     if (tj[c] >= 0) {
       exec_ids[(size_t)t * K + tj[c]] = ov[c];
-      exec_gates[(size_t)t * K + tj[c]] = (flags & FLAG_UNIT_GATES) ? 1.0f : xv[c] / Ssum;
+      exec_gates[(size_t)t * K + tj[c]] = xv[c] / Ssum;
     }
   }
   if (lane < K && lane >= nx) {
@@ -689,7 +688,8 @@ constexpr int CP_PAIRS = MAX_B * MAX_K;   // routed pairs at most
 // die, each making the whole sort (the same arithmetic, so the same result
 // everywhere) and writing its die's header, units and token rows, which the
 // FFN's workgroups on that die then read from their own L2; workgroup 0
-// alone writes the plan.  Without tables, one workgroup.
+// alone writes the plan.  With the split kernels' records (rec) the same, each
+// workgroup writing its die's records and token list; with neither, one workgroup.
 // The routed pairs are taken in flat order q = t K + j, so sorting by (slot,
 // q) is sorting by (slot, token, rank).  Wavefront w owns the pairs w 64 PPT
 // + r 64 + lane (r = 0 .. PPT - 1, PPT pairs per thread, PPT * CP_THREADS >=
@@ -1078,14 +1078,14 @@ void k_compact(int B, int K, uint64_t kmul, int E, int budget, int ns,
 // 64-token chunk, at most PL_THREADS routed pairs) in one launch, for the
 // fused layer, whose routes are distinct.  One workgroup per die (one in all
 // without rec) makes the whole plan -- the arithmetic and the order of
-// select_body and k_select_backfill, so the same results -- and writes its
+// select_body, select_rank and k_select_backfill, so the same results -- and writes its
 // die's slot records; workgroup 0 writes the plan.
 //  * A thread brings one routed pair; its cost goes to V[u][t].  PL_T (32 or
 //    64) token positions: the tree of a chunk whose upper positions are +0 is
 //    that of the lower ones (a cost is never -0).  Four lanes per expert: lane
 //    p holds the positions p, p + 4, .., so that the tree's levels down to 4
 //    are its own and 2, 1 lane exchanges.
-//  * The kept experts' ranks as in select_body.
+//  * The kept experts' ranks as in select_rank.
 //  * A wavefront backfills the tokens wv, wv + 16, ..; executing slot s sets
 //    bit t of mask[s], so that a pair's place is the slot's offset plus the
 //    bits below its own: the sort by (slot, token) without counting passes.
@@ -1187,7 +1187,7 @@ void k_plan_split(int B, int K, int E, int budget, int ns, int binary, int flags
   const int n_sel = min(budget, n_union);
   {
     // tpe consecutive threads per expert over interleaved key pairs, as in
-    // select_body
+    // select_rank
     int E2 = WAVE;
     while (E2 < E) E2 <<= 1;
     const int tpe = PL_THREADS / E2, npair = E2 / (2 * tpe);

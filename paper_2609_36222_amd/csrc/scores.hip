@@ -4,13 +4,17 @@
 // k_scores  the router's dot products for a batch, as a tiled batch x rows
 //           product: logit l[t][e] = x_t . W_r[e] + beta_e (and, with shared
 //           experts gated by a vector, gdot[t] = x_t . g).
+// k_scores_small  the same straight into registers, for few dot products; for
+//           the fused layer's small batches also the predictor's dot products
+//           with every expert and ||x||^2.
 // k_tail    one workgroup per token: top-K by exact ranks, router weights,
 //           then the score of each routed pair.  For the method's own rule
-//           the pair's predicted removal cost w^2 exp(q / ||x|| + b_u),
-//           q = a_u . x_t, is computed here for the K routed experts only
-//           (App. "Custom GPU Kernels": the token is normalised once and
-//           reused across its K experts), wavefront w taking routes 2w and
-//           2w + 1; the other rules need only the routes.
+//           the pair's predicted removal cost w^2 exp(q / ||x|| + b_u), q =
+//           a_u . x_t, from k_scores_small's dot products or else from ones
+//           made here for the K routed experts only (App. "Custom GPU
+//           Kernels": the token is normalised once and reused across its K
+//           experts), wavefront w taking routes 2w and 2w + 1; the other
+//           rules need only the routes.
 //
 // Fixed fp32 order of every dot product of length d: partial j (0..63) owns
 // the elements 256m + 4j + r (r = 0..3) and accumulates them in ascending
@@ -319,7 +323,9 @@ void k_scores_small(const XT *__restrict__ x, int B, int d, const float *__restr
       if (m0 + SS_GC * 256 < d) add(1, m0 + SS_GC * 256);
     }
   };
-  if (extra) {   // rows: 0 x itself, 1 G
+  // rows: 0 x itself (also where ss is not asked for: its FMAs hide behind the
+  // loads), 1 G
+  if (extra) {
     stream(
         [&](int s, int c, int m) {
           wv[s][c][0] = G ? *reinterpret_cast<const float4 *>(wr[0] + m) : float4{0.f, 0.f, 0.f, 0.f};
@@ -399,8 +405,8 @@ __device__ __forceinline__ float pair_cost(float q, float ss, float b, float w) 
 // mode bit 0: route (top-K and weights from the logits into ids / w)
 // mode bit 1: per-pair scores of the routed pairs (ids / w, read back when
 //             bit 0 is off) under `rule`: SCORE_BASE w^2 exp(q / ||x|| + b_u)
-//             with q = a_u . x_t and ||x_t||^2 computed here in the fixed
-//             order; SCORE_TOP1 1 for the first route, else 0; SCORE_WEIGHT
+//             with q = a_u . x_t and ||x_t||^2 in the fixed order, read (qd,
+//             ssd: k_scores_small's) or computed here; SCORE_TOP1 1 for the first route, else 0; SCORE_WEIGHT
 //             w; SCORE_WEIGHT_SQ w * w; SCORE_STATIC (w * w) * exp(b_u)
 // One workgroup of tail_waves(K, pred) wavefronts per token, token group g on
 // die g % N_XCD as in k_scores (xcd_group).  Top-K in the
@@ -410,7 +416,7 @@ __device__ __forceinline__ float pair_cost(float q, float ss, float b, float w) 
 // equal stretches of the keys (E2 the power of two >= E, C = min(TL_RANK /
 // E2, E2)); route k is the expert of rank k.  Every wavefront then takes the
 // routes and weights from LDS; wavefront w computes the predictor of routes
-// 2w and 2w + 1.
+// 2w and 2w + 1 (without qd).
 template <typename XT>
 __global__ __launch_bounds__(TL_MAXW * WAVE)
 void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__ logits,
