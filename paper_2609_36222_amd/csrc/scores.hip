@@ -406,8 +406,9 @@ __device__ __forceinline__ float pair_cost(float q, float ss, float b, float w) 
 // mode bit 1: per-pair scores of the routed pairs (ids / w, read back when
 //             bit 0 is off) under `rule`: SCORE_BASE w^2 exp(q / ||x|| + b_u)
 //             with q = a_u . x_t and ||x_t||^2 in the fixed order, read (qd,
-//             ssd: k_scores_small's) or computed here; SCORE_TOP1 1 for the first route, else 0; SCORE_WEIGHT
-//             w; SCORE_WEIGHT_SQ w * w; SCORE_STATIC (w * w) * exp(b_u)
+//             ssd: k_scores_small's) or computed here; SCORE_TOP1 1 for the
+//             first route, else 0; SCORE_WEIGHT w; SCORE_WEIGHT_SQ w * w;
+//             SCORE_STATIC (w * w) * exp(b_u)
 // One workgroup of tail_waves(K, pred) wavefronts per token, token group g on
 // die g % N_XCD as in k_scores (xcd_group).  Top-K in the
 // order (logit desc, index asc) of rank_key: the token's keys go to LDS and
@@ -417,7 +418,10 @@ __device__ __forceinline__ float pair_cost(float q, float ss, float b, float w) 
 // E2, E2)); route k is the expert of rank k.  Every wavefront then takes the
 // routes and weights from LDS; wavefront w computes the predictor of routes
 // 2w and 2w + 1 (without qd).
-template <typename XT>
+// DENSE: the method's rule on k_scores_small's dot products (qd, ssd); an
+// instance of its own: the others carried its registers and LDS for 0.1 to 0.2
+// us of a base_route of 8 to 13.
+template <typename XT, bool DENSE>
 __global__ __launch_bounds__(TL_MAXW * WAVE)
 void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__ logits,
             const XT *__restrict__ x, const float *__restrict__ A,
@@ -429,14 +433,14 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
   __shared__ float lrow[MAX_E];
   __shared__ int part[TL_RANK];
   __shared__ int route[MAX_K];
-  __shared__ float qrow[MAX_E];
+  __shared__ float qrow[DENSE ? MAX_E : 1];
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id_u();
   int tg, ti;
   xcd_group(blockIdx.x, TOK_GROUP, tg, ti);
   const int t = tg * TOK_GROUP + ti;   // on the die that wrote its logits
   if (t >= B) return;
   // the predictor's dot products: made here, or (qd, ssd) by k_scores_small
-  const bool pred = (mode & 2) && rule == SCORE_BASE && !qd;
+  const bool pred = !DENSE && (mode & 2) && rule == SCORE_BASE;
   // the logits row (clamped, no branches, so that the loads are in flight
   // together); the method's predictor's first pass of the token row is
   // requested once the routing's inputs have arrived (it does not depend on
@@ -447,7 +451,7 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
     for (int i = 0; i < TL_NI; ++i) lv[i] = logits[(size_t)t * E + min(lane + WAVE * i, E - 1)];
   }
   float qv[TL_NI], ssv = 0.0f;
-  if (qd && w == 0) {   // written on other dies: they arrive while the routing runs
+  if (DENSE && w == 0) {   // written on other dies: they arrive while the routing runs
 #pragma unroll
     for (int i = 0; i < TL_NI; ++i) qv[i] = qd[(size_t)t * E + min(lane + WAVE * i, E - 1)];
     ssv = ssd[t];
@@ -545,7 +549,7 @@ void k_tail(int B, int E, int K, int d, int norm_topk, const float *__restrict__
   if (!(mode & 2)) return;
 
   const int u = (lane < K && my_id >= 0 && my_id < E) ? my_id : 0;   // out-of-range ids read row 0
-  if (qd) {   // the method's rule on k_scores_small's dot products
+  if constexpr (DENSE) {   // the method's rule on k_scores_small's dot products
     if (w != 0) return;
 #pragma unroll
     for (int i = 0; i < TL_NI; ++i)
@@ -652,12 +656,17 @@ hipError_t launch_tail(bool bf16, int B, int E, int K, int d, int norm_topk,
                        const float *ss) {
   const dim3 block(tail_waves(K, (mode & 2) && rule == SCORE_BASE && !q) * WAVE);
   const dim3 grid(xcd_grid((B + TOK_GROUP - 1) / TOK_GROUP, TOK_GROUP));
-  if (bf16)
-    launch_k(k_tail<uint16_t>, grid, block, 0, st, B, E, K, d, norm_topk, logits,
-             (const uint16_t *)x, A, bp, ids, w, cost, mode, rule, order, ex, den, q, ss);
-  else
-    launch_k(k_tail<float>, grid, block, 0, st, B, E, K, d, norm_topk, logits,
-             (const float *)x, A, bp, ids, w, cost, mode, rule, order, ex, den, q, ss);
+#define BASE_TL(XT, D)                                                                          \
+  launch_k(k_tail<XT, D>, grid, block, 0, st, B, E, K, d, norm_topk, logits, (const XT *)x, A, \
+           bp, ids, w, cost, mode, rule, order, ex, den, q, ss)
+  if (bf16) {
+    if (q) BASE_TL(uint16_t, true);
+    else BASE_TL(uint16_t, false);
+  } else {
+    if (q) BASE_TL(float, true);
+    else BASE_TL(float, false);
+  }
+#undef BASE_TL
   return hipGetLastError();
 }
 
