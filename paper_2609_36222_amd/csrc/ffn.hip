@@ -525,16 +525,20 @@ constexpr int SPG_RT = 2, SPG_DW = 4;
 constexpr int SPD_RT1 = 2, SPD_RT2 = 4, SPD_DW = 4;
 static_assert(FFN_SPLIT_B <= 4 * 16, "a slot's pairs in one pass");
 
-// Slot y of the launch: kept slots 0 .. slots - 1, then the shared experts;
-// this workgroup's die's copy of the records.
+// Slot y of the launch: the shared experts, then kept slots 0 .. slots - 1;
+// this workgroup's die's copy of the records.  The shared experts run for every
+// token, so theirs are the longest workgroups and start first: last, as their
+// records lie, they were the launch's tail (two and four shared experts of d =
+// 2048, I = 1408, 16 and 8 kept, base_moe_forward at B = 64 88.7 and 66.8 us, now
+// 81.3 and 63.5; row-major at B = 48 90.3 and 74.8, now 84.9 and 65.9; one token
+// tile a slot, B <= 16, the same).
 struct SpSlot {
   int u, p0, n;
 };
 __device__ __forceinline__ int sp_die() { return (blockIdx.x + gridDim.x * blockIdx.y) % N_XCD; }
-__device__ __forceinline__ SpSlot sp_slot(int slots, int budget, int nrec,
-                                          const SpRec *__restrict__ rec) {
-  const int s = blockIdx.y;
-  const SpRec r = rec[sp_die() * nrec + (s < slots ? s : budget + (s - slots))];
+__device__ __forceinline__ SpSlot sp_slot(int budget, int nrec, const SpRec *__restrict__ rec) {
+  const int s = blockIdx.y, ns = nrec - budget;
+  const SpRec r = rec[sp_die() * nrec + (s < ns ? budget + s : s - ns)];
   return {__builtin_amdgcn_readfirstlane(r.u), __builtin_amdgcn_readfirstlane(r.p0),
           __builtin_amdgcn_readfirstlane(r.n)};
 }
@@ -692,13 +696,13 @@ __device__ __forceinline__ void gateup_split(f32x4 *red, int d, int I, const uin
 // NT: token tiles per pass (1, 2 or 4); RT row-pair tiles per workgroup
 template <int NT, int RT, bool PACKED>
 __global__ __launch_bounds__(SP_WAVES * WAVE)
-void k_gateup_split(int d, int I, int E, int slots, int budget, int nrec, int np,
+void k_gateup_split(int d, int I, int E, int budget, int nrec, int np,
                     const uint16_t *__restrict__ w13r, const uint16_t *__restrict__ w13s,
                     const SpRec *__restrict__ rec, const int32_t *__restrict__ sptok,
                     const uint16_t *__restrict__ x, int B, uint16_t *__restrict__ H) {
   constexpr int KIB = sp_kib<2 * RT, NT, PACKED>();
   __shared__ f32x4 red[SP_WAVES * KIB * WAVE];
-  const SpSlot sl = sp_slot(slots, budget, nrec, rec);
+  const SpSlot sl = sp_slot(budget, nrec, rec);
   const int32_t *tok = sptok + (size_t)sp_die() * np + sl.p0;
   const int lane = lane_id(), rp0 = blockIdx.x * RT;
   const uint16_t *w13 = sl.u < E ? w13r + (size_t)sl.u * 2 * I * d
@@ -781,13 +785,13 @@ __device__ __forceinline__ void down_split(f32x4 *red, int d, int I, const uint1
 
 template <int NT, int RT, bool PACKED>
 __global__ __launch_bounds__(SP_WAVES * WAVE)
-void k_down_split(int d, int I, int E, int slots, int budget, int nrec,
+void k_down_split(int d, int I, int E, int budget, int nrec,
                   const uint16_t *__restrict__ w2r, const uint16_t *__restrict__ w2s,
                   const SpRec *__restrict__ rec, const float *__restrict__ pair_gate, const uint16_t *__restrict__ H,
                   float *__restrict__ pairbuf) {
   constexpr int KIB = sp_kib<RT, NT, PACKED>();
   __shared__ f32x4 red[SP_WAVES * KIB * WAVE];
-  const SpSlot sl = sp_slot(slots, budget, nrec, rec);
+  const SpSlot sl = sp_slot(budget, nrec, rec);
   const uint16_t *w2 = sl.u < E ? w2r + (size_t)sl.u * d * I : w2s + (size_t)(sl.u - E) * d * I;
   for (int c = 0; c < sl.n; c += 16 * NT) {
     const int n = min(sl.n - c, 16 * NT), p0 = sl.p0 + c, rt0 = blockIdx.x * RT;
@@ -973,7 +977,7 @@ hipError_t launch_gateup(bool bf16, bool packed, const void *x, int B, int d,
                       : B <= 32 ? (packed ? BASE_GS(2, true) : BASE_GS(2, false))
                                 : (packed ? BASE_GS(4, true) : BASE_GS(4, false));
 #undef BASE_GS
-    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, budget + ns,
+    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, budget, budget + ns,
              B * (K + ns), (const uint16_t *)w13, (const uint16_t *)w13s, rec, sptok,
              (const uint16_t *)x, B, (uint16_t *)H);
   } else if (bf16) {
@@ -1003,7 +1007,7 @@ hipError_t launch_down(bool bf16, bool packed, int B, int d, int I, int E, int K
                       : B <= 32 ? (packed ? BASE_DS(2, SPD_RT2, true) : BASE_DS(2, SPD_RT2, false))
                                 : (packed ? BASE_DS(4, SPD_RT2, true) : BASE_DS(4, SPD_RT2, false));
 #undef BASE_DS
-    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, slots, budget, budget + ns,
+    launch_k(kern, grid, dim3(SP_WAVES * WAVE), 0, st, d, I, E, budget, budget + ns,
              (const uint16_t *)w2, (const uint16_t *)w2s, rec, pair_gate, (const uint16_t *)H, pairbuf);
   } else if (bf16) {
     const int kind = ffn_dn_kind(budget, ns, I);
