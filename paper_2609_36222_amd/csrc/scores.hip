@@ -619,7 +619,7 @@ template <typename XT>
 static void launch_scores_t(const XT *x, int B, int d, const float *Wr, const float *beta,
                             int n_router, const float *G, float *logits, float *gdot,
                             const float *A, float *q, float *ss, hipStream_t st) {
-  if (A || scores_small_router(B, n_router, d)) {
+  if (A || scores_small_router(sizeof(XT) == 2, B, n_router, d)) {
     const int n_group = (B + TOK_GROUP - 1) / TOK_GROUP, rgs = (n_router + 3) / 4;
     const int n_other = n_group * ((A ? rgs : 0) + (A || G ? 1 : 0));
     int nb;   // workgroups per die

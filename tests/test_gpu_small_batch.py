@@ -120,6 +120,7 @@ def test_scores_lines(gu, B, d, E):  # noqa: F811
     """Either side of the lines between the scoring kernels, with the
     predictor's rows in the same launch and without; a gate alone."""
     _small_scores(gu, B, d, E, True, 1)
+    _small_scores(gu, B, d, E, False, 0)
 
 
 def _small_scores(gu, B, d, E, bf16, sg):  # noqa: F811
