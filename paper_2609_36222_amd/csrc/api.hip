@@ -477,7 +477,7 @@ base_status base_decode_layer(const base_layer *L, const void *x, int32_t B,
   stage(0, st);
   // a small batch's launch also makes the predictor's dot products: q lies in
   // the pair rows' buffer and ||x||^2 in the activations', free until the FFN
-  const bool dense = scores_dense(B, L->E, L->d) && L->score_rule == BASE_SCORE_BASE;
+  const bool dense = scores_small(B, L->E) && L->score_rule == BASE_SCORE_BASE;
   float *qd = dense ? at<float>(ws, o.pairbuf) : nullptr, *ss = dense ? at<float>(ws, o.H) : nullptr;
   HIP_TRY(launch_scores(bf16, x, B, L->d, L->w_router, L->b_router, L->E, shared_gate(L),
                         logits, at<float>(ws, o.gdot), st, dense ? L->pred_a : nullptr, qd, ss));

@@ -197,20 +197,10 @@ __host__ __device__ inline unsigned ffn_dn_grid(int n_cu, int kind) {
 }
 
 // Few dot products: k_scores_small, which may also take the predictor's rows.
-// With the predictor (scores_dense) the line is B <= 64 or B E <= 64 * 128 (its
-// comment in scores.hip has both sides), but four token groups against 128 or
-// more long rows leave the predictor more workgroups on the four free dies than
-// they have CUs: from B = 49 the tail's rows, K a token, are the faster there
-// (the layer at B = 64, K = 1 and 8, two kept experts of I = 64, in us: E = 128,
-// d = 2048 36.5 and 41.5 -> 35.0 and 41.2; E = 256, d = 4096 57.4 and 65.4 ->
-// 53.3 and 62.8; but E = 64, d = 16384 98.0 and 125.9 in the tail, 93.3 and
-// 117.5 here, E = 200, d = 1024 40.5 and 38.8, E = 256, d = 2048, B = 48 44.8 and
-// 43.3).
+// With the predictor the line is B <= 64 or B E <= 64 * 128 (its comment in
+// scores.hip has both sides).
 constexpr int SC_SMALL_B = 64, SC_SMALL_DOTS = 64 * 128;
 inline bool scores_small(int B, int E) { return B <= SC_SMALL_B || B * E <= SC_SMALL_DOTS; }
-inline bool scores_dense(int B, int E, int d) {
-  return scores_small(B, E) && !(B > 48 && E >= 128 && d >= 2048);
-}
 // Without the predictor (base_route, the other rules, a gate alone with E = 0)
 // the tiles win for bf16 tokens where a wavefront's ring has nothing to hide, d
 // <= 512 from a whole token group on, and past 128 rows (base_route, us, tiled
@@ -225,7 +215,7 @@ inline bool scores_small_router(bool bf16, int B, int E, int d) {
          (!bf16 || (E <= 128 ? B < TOK_GROUP || d > 512 : B < TOK_GROUP && d > 512));
 }
 // rows: n_router of Wr (logits, + beta), then the vector G when given (gdot);
-// scores_dense launches may also take the predictor's rows A [n_router]: the
+// scores_small launches may also take the predictor's rows A [n_router]: the
 // dot products of every expert (q [B][n_router]) and ||x||^2 (ss [B])
 hipError_t launch_scores(bool bf16, const void *x, int B, int d, const float *Wr,
                          const float *beta, int n_router, const float *G, float *logits,

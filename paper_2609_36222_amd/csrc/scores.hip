@@ -219,7 +219,7 @@ void k_scores(const XT *__restrict__ x, int B, int d,
   }
 }
 
-// Few dot products (scores_dense, scores_small_router).  The tiled kernel's few workgroups (16 at B
+// Few dot products (scores_small, scores_small_router).  The tiled kernel's few workgroups (16 at B
 // <= 16, on one die) walk their chunks behind LDS barriers; here a wavefront
 // takes 4 tokens x 4 rows straight into registers, SS_GC chunks of 256
 // elements at a time with the next ones in flight, and nothing is shared, so
@@ -244,7 +244,7 @@ void k_scores(const XT *__restrict__ x, int B, int d,
 // wavefront) catch up with what the tiles save (E = 128: layer at B = 80 66.4
 // tiled, 67.7 here; B = 128 87.8, 87.2; B = 256 111, 115), below they gain (E =
 // 64: B = 72 76.9 -> 73.8, B = 128 84.2 -> 81.4; E = 8, d = 4096: B = 128 299.7
-// -> 293.6, B = 1000 1041 -> 1036); what it excepts: scores_dense,
+// -> 293.6, B = 1000 1041 -> 1036); what it excepts:
 // scores_small_router.  Four chunks at a time: equal, slower at d = 256.
 constexpr int SS_GC = 2;
 

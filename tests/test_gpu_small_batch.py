@@ -114,8 +114,7 @@ def test_small_scores_of_many_tokens(gu, B, E):  # noqa: F811
 
 
 @pytest.mark.parametrize("B,d,E", [(8, 256, 129), (8, 768, 129), (15, 512, 128), (16, 512, 128),
-                                   (16, 768, 128), (16, 768, 129), (48, 2048, 128),
-                                   (49, 1792, 128), (49, 2048, 127), (49, 2048, 128)])
+                                   (16, 768, 128), (16, 768, 129)])
 def test_scores_lines(gu, B, d, E):  # noqa: F811
     """Either side of the lines between the scoring kernels, with the
     predictor's rows in the same launch and without; a gate alone."""
