@@ -219,19 +219,19 @@ void k_scores(const XT *__restrict__ x, int B, int d,
   }
 }
 
-// Few dot products (scores_small, scores_small_router).  The tiled kernel's few workgroups (16 at B
-// <= 16, on one die) walk their chunks behind LDS barriers; here a wavefront
-// takes 4 tokens x 4 rows straight into registers, SS_GC chunks of 256
-// elements at a time with the next ones in flight, and nothing is shared, so
-// the launch is a ring of loads (d = 2048: four stages, two of them in flight
+// Few dot products (scores_small, scores_small_router).  The tiled kernel's few
+// workgroups (16 at B <= 16, on one die) walk their chunks behind LDS barriers;
+// here a wavefront takes 4 tokens x 4 rows straight into registers, SS_GC chunks
+// of 256 elements at a time with the next ones in flight, and nothing is shared,
+// so the launch is a ring of loads (d = 2048: four stages, two of them in flight
 // at once), 64 FMAs a chunk and a tree.  With the chip
 // otherwise idle it also makes the predictor's dot products with every
 // expert (A, q) and ||x||^2 (ss), which k_tail would otherwise start only once
 // the routing is known.  Each dot product in the fixed order.  The extra rows
 // go through the same ring (as a plain loop, one round trip a chunk, they were
-// the launch's longest wavefronts: the Mixtral-shaped d = 4096 layer with a
-// gate, staged at B = 16, 27.2 us, now 26.6; d = 16384 at B = 1 48.6 and 46.4,
-// the whole layer 65.1 and 58.1).
+// the launch's longest wavefronts: d = 4096, a staged layer with a gate, B = 16,
+// 27.2 us, now 26.6; d = 16384 at B = 1 48.6 and 46.4, the fused layer 65.1 and
+// 58.1).
 // A workgroup is 4 wavefronts: 16 tokens (a token group) x 4 rows.  The router
 // rows of token group g run on die g % N_XCD, where k_tail reads the logits;
 // the predictor's and the extra rows (G; x itself) on the dies without a token
