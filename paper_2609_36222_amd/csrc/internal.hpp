@@ -209,16 +209,18 @@ constexpr int SC_SMALL_B = 64, SC_SMALL_DOTS = 64 * 128;
 inline bool scores_small(int B, int E) { return B <= SC_SMALL_B || B * E <= SC_SMALL_DOTS; }
 // Without the predictor (base_route, the other rules, a gate alone with E = 0)
 // the tiles win for bf16 tokens where a wavefront's ring has nothing to hide, d
-// <= 512 from a whole token group on, and past 128 rows (base_route, us, tiled
-// against small: E = 64, B = 16 d = 256 5.4 and 5.7, d = 1024 6.5 and 6.2, d =
-// 4096 12.2 and 9.6; E = 64, B = 8, d = 512 5.8 and 5.2; E = 160, B = 32 d = 512
-// 8.9 and 9.8, d = 2048 12.4 and 12.3; E = 256, B = 8 d = 256 8.0 and 8.6, d = 2048
-// 12.4 and 10.5; a gate alone, the staged call, B = 300 d = 256 26.3 and 27.3, d =
-// 4096 65.0 and 62.6).  fp32 tokens, twice the bytes to stage, never (E = 1, B = 64,
-// d = 256 6.4 and 5.5; E = 256, B = 64 d = 256 10.4 and 9.7, d = 2048 24.7 and 13.3).
+// <= 512, and past 128 rows, both with more tokens than two wavefronts of a group
+// take (base_route, us, tiled against small: E = 64, B = 16 d = 256 5.4 and 5.7, d
+// = 1024 6.5 and 6.2, d = 4096 12.2 and 9.6; E = 64, B = 8, d = 512 5.8 and 5.2; E =
+// 3, B = 13, d = 256 4.9 and 5.6; E = 135, B = 13, d = 1536 10.6 and 11.6; E = 160, B
+// = 32 d = 512 8.9 and 9.8, d = 2048 12.4 and 12.3; E = 256, B = 8 d = 256 8.0 and
+// 8.6, d = 2048 12.4 and 10.5; a gate alone, the staged call, B = 300 d = 256 26.3
+// and 27.3, d = 4096 65.0 and 62.6).  fp32 tokens, twice the bytes to stage, never
+// (E = 1, B = 64, d = 256 6.4 and 5.5; E = 256, B = 64 d = 256 10.4 and 9.7, d = 2048
+// 24.7 and 13.3).
 inline bool scores_small_router(bool bf16, int B, int E, int d) {
-  return scores_small(B, E) &&
-         (!bf16 || (E <= 128 ? B < TOK_GROUP || d > 512 : B < TOK_GROUP && d > 512));
+  const bool few = E <= 128, ring = d > 512;
+  return scores_small(B, E) && (!bf16 || (B <= TOK_GROUP / 2 ? few || ring : few && ring));
 }
 // rows: n_router of Wr (logits, + beta), then the vector G when given (gdot);
 // scores_small launches may also take the predictor's rows A [n_router]: the

@@ -113,8 +113,8 @@ def test_small_scores_of_many_tokens(gu, B, E):  # noqa: F811
     _small_scores(gu, B, 512, E, True, 1)
 
 
-@pytest.mark.parametrize("B,d,E", [(8, 256, 129), (8, 768, 129), (15, 512, 128), (16, 512, 128),
-                                   (16, 768, 128), (16, 768, 129)])
+@pytest.mark.parametrize("B,d,E", [(8, 256, 129), (8, 768, 129), (8, 512, 128), (9, 512, 128),
+                                   (9, 768, 128), (9, 768, 129)])
 def test_scores_lines(gu, B, d, E):  # noqa: F811
     """Either side of the lines between the scoring kernels, with the
     predictor's rows in the same launch and without; a gate alone."""
